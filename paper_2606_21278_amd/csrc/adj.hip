@@ -8,9 +8,10 @@
 // Step 4) made Hermitian, and the same times i kx and i ky, each brought to the
 // grid by an inverse FFT; the points then gather W x W taps from each grid with
 // the same spreading kernel.  The three grids of a whole cell do not fit in
-// LDS, so each work item rebuilds one row band (plus the kernel's halo) and
-// serves the points whose footprint starts in that band.  Nothing of the
-// forward pass is stored.
+// LDS: one launch transforms the columns of every cell (adj_cols_kernel), then
+// each work item of the next builds one row band of the grids (plus the
+// kernel's halo) from them and serves the points whose footprint starts in
+// that band.  Nothing of the forward pass is stored.
 #include <algorithm>
 #include <string>
 
@@ -20,44 +21,11 @@
 
 namespace enufft {
 
-struct AdjLayout {
-  int rows;       // band rows including halo = band_rows + W
-  int apitch;     // grid row pitch (elements) = n1 + W - 1, rounded up to even: the first W - 1
-                  // columns are repeated after the last, so a footprint's W columns are contiguous
-  int cpitch;     // column-workspace pitch (elements) = 2 (K1 + 1) + 2
-  size_t g_off, gx_off, gy_off, db0_off, db1_off, ws_off;   // element offsets
-  size_t st_off;  // staged cell spectrum, deconvolution factors and keep bytes
-  size_t tw_off;  // twiddles of the row (n1) and column (n2) transforms, interleaved complex
-  size_t total;   // elements
-};
-
 // Elements of the staging area: the cell's N1 N2 complex coefficients, the
 // K1 + 1 and K2 + 1 deconvolution factors, then N1 N2 keep bytes.
 __host__ __device__ inline size_t adj_stage_elems(const Geom &g, size_t elem) {
   const size_t M = (size_t)g.N1 * g.N2;
   return 2 * M + (g.K1 + 1) + (g.K2 + 1) + (M + elem - 1) / elem;
-}
-
-__host__ __device__ inline AdjLayout adj_layout(const Geom &g, int W, int band_rows, size_t elem) {
-  AdjLayout L;
-  L.rows = band_rows + W;   // R + W - 1 rows are used; one more keeps the uy rows paired
-  L.apitch = (g.n1 + W - 1 + 1) & ~1;
-  L.cpitch = 2 * (g.K1 + 1) + 2;
-  const size_t gsz = (size_t)L.rows * L.apitch;
-  L.g_off = 0;
-  L.gx_off = gsz;
-  L.gy_off = 2 * gsz;
-  // the column workspace and the staging area behind it alias the grids (they
-  // are dead before the grids are written) but never the band spectra, which
-  // are filled while they are live
-  const size_t ws = (size_t)g.n2 * L.cpitch;
-  L.ws_off = 0;
-  L.st_off = ws;
-  L.db0_off = std::max(3 * gsz, ws + adj_stage_elems(g, elem));
-  L.db1_off = L.db0_off + (size_t)L.rows * (g.K1 + 1) * 2;
-  L.tw_off = L.db1_off + (size_t)L.rows * (g.K1 + 1) * 2;
-  L.total = L.tw_off + 2 * (size_t)(g.n1 + g.n2);
-  return L;
 }
 
 // Copy the cell's cotangent spectrum, its keep bytes and the deconvolution
@@ -274,12 +242,534 @@ __device__ __forceinline__ void row_ifft_natural(int n, int count, const T *tw, 
 }
 
 // First-step accessor of the row transforms: load(k) forms bin k of the row's
-// spectrum from the band's column data db ([row][kx] complex, kx = 0..K1):
-// for a (u, du/dx) row, (1 - k) D(k); for a du/dy pair (rows row, row + 1),
-// D_row(k) + i D_row+1(k); D(-k) = conj D(k), zero beyond K1.  store() writes
-// the grid row like StridedPairAcc.
+// spectrum from column data db ([row][kx] complex, kx = 0..K1): for a (u, du/dx)
+// row, (1 - k) D(k); for a pair of rows (row, row + 1), D_row(k) + i D_row+1(k);
+// D(-k) = conj D(k), zero beyond K1.  store() writes the grid row like
+// StridedPairAcc.  The loads are unconditional (bins beyond K1 read bin K1), so
+// those of one transform are in flight together when db is global memory.
 template <typename T>
 struct RowSpecAcc {
+  const T *db;
+  T *r0, *r1;
+  int stride, row, per, n1, K1;
+  bool pair;
+  __device__ void load(int k, T &re, T &im) const {
+    using V2 = typename vec2<T>::type;
+    const int kk = k <= n1 / 2 ? k : n1 - k;
+    const bool neg = k != kk, in = kk <= K1;
+    const V2 *d = reinterpret_cast<const V2 *>(db) + (row * per + (in ? kk : K1));
+    const V2 v = d[0];
+    const T di = neg ? -v.y : v.y;
+    if (!pair) {
+      const T kf = neg ? -T(kk) : T(kk);
+      re = in ? v.x - kf * v.x : T(0);
+      im = in ? di - kf * di : T(0);
+    } else {
+      const V2 w = d[per];
+      const T bi = neg ? -w.y : w.y;
+      re = in ? v.x - bi : T(0);
+      im = in ? di + w.x : T(0);
+    }
+  }
+  __device__ void store(int i, T re, T im) const {
+    r0[i * stride] = re;
+    r1[i * stride] = im;
+  }
+};
+
+// ------------------------------------------------------------------ banded adjoint
+
+// First-step accessor of the column transforms from global memory: as
+// ColSpecAcc, reading the cell's coefficients, keep bytes and deconvolution
+// factors in place.  Loads are unconditional (bins outside the box read mode 0
+// and are masked), so those of one transform are in flight together.
+template <typename T>
+struct ColSpecGlobal {
+  const typename vec2<T>::type *sf;
+  const T *dx, *dy;
+  const uint8_t *kp;
+  T two_lam;
+  T *col;
+  int cpitch, kx, n2, K2, N1, lo1, lo2, hi1, hi2;
+  bool yderiv;
+  __device__ void load(int bin, T &re, T &im) const {
+    const int ky = bin <= n2 / 2 ? bin : bin - n2;
+    const bool in = ky >= -K2 && ky <= K2;
+    const bool p = in && kx <= hi1 && ky >= lo2 && ky <= hi2;
+    const bool q = in && -kx >= lo1 && -ky >= lo2 && -ky <= hi2;
+    const int mp = p ? (ky - lo2) * N1 + (kx - lo1) : 0, mq = q ? (-ky - lo2) * N1 + (-kx - lo1) : 0;
+    const auto vp = sf[mp], vq = sf[mq];
+    T sp = T(1), sq = T(1);
+    if (kp) {
+      sp = kp[mp] ? two_lam : T(0);
+      sq = kp[mq] ? two_lam : T(0);
+    }
+    const T s = T(0.5) * (dx[kx] * dy[in ? (ky < 0 ? -ky : ky) : 0]);
+    T hr = p ? sp * vp.x : T(0), hi = p ? sp * vp.y : T(0);
+    hr += q ? sq * vq.x : T(0);
+    hi -= q ? sq * vq.y : T(0);
+    hr *= s;
+    hi *= s;
+    re = !in ? T(0) : yderiv ? -T(ky) * hi : hr;
+    im = !in ? T(0) : yderiv ? T(ky) * hr : hi;
+  }
+  __device__ void store(int i, T re, T im) const {
+    col[i * cpitch] = re;
+    col[i * cpitch + 1] = im;
+  }
+};
+
+constexpr int ADJ_COLS_THREADS = 192;
+constexpr int ADJ_COLS_GROUP = 12;   // columns of one workgroup, at most
+
+__host__ __device__ inline int adj_col_groups(const Geom &g) {
+  return (g.K1 + 1 + ADJ_COLS_GROUP - 1) / ADJ_COLS_GROUP;
+}
+
+// Column spectra of the cells cell0 .. : a.cols holds, per cell, `nset` blocks
+// [n2][K1 + 1] complex, the inverse transforms along y of the pre-corrected
+// spectrum (set 0) and of i ky times it (set 1).  One workgroup per (cell, set,
+// group of up to 12 columns): the columns are independent, so a call with few
+// cells still fills many CUs.  They are transformed once per cell here: inside the
+// band kernel every band (32 of four rows each in FP64 at 64 x 64 modes and W = 12,
+// whose column workspace left no room for more) and every chunk of a cell had
+// repeated both column passes.  64 hexagons of 2.07e6 unordered samples in all, FP64,
+// 64 x 64 modes, W = 12: this launch 16 us, the bands' 324 us (four bands of 32
+// rows); the one launch before took 10.0 ms, with the exact kernel (a square root, a
+// division and an exponential per tap) and one lane in 32 gathering.
+template <typename T>
+__global__ __launch_bounds__(ADJ_COLS_THREADS) void adj_cols_kernel(AdjArgs<T> a, int nset) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  constexpr int NT = ADJ_COLS_THREADS;
+  const Geom &g = a.g;
+  const int per = g.K1 + 1, ngrp = adj_col_groups(g), cg = (per + ngrp - 1) / ngrp;
+  const int n2 = g.n2, A = fft_A(n2), B = fft_B(n2);
+  int b = blockIdx.x;
+  const int grp = b % ngrp;
+  b /= ngrp;
+  const int set = b % nset, lc = b / nset, cell = a.cell0 + lc;
+  const int c0 = grp * cg, nc = min(cg, per - c0);
+  if (nc <= 0) return;
+  T *tw2 = reinterpret_cast<T *>(smem_raw), *ws = tw2 + 2 * n2;
+  for (int i = threadIdx.x; i < 2 * n2; i += NT) tw2[i] = a.tw2[i];
+  __syncthreads();
+  ColSpecGlobal<T> acc;
+  acc.sf = reinterpret_cast<const typename vec2<T>::type *>(a.fbar) + (int64_t)cell * g.N1 * g.N2;
+  acc.dx = a.decon_x;
+  acc.dy = a.decon_y;
+  acc.kp = a.keep ? a.keep + (int64_t)cell * g.N1 * g.N2 : nullptr;
+  // the reconstruction's coefficients are kept or dropped, not weighted
+  acc.two_lam = a.rec_part ? T(1) : T(2.0 * (a.lam ? a.lam[cell] : 1.0));
+  acc.cpitch = 2 * cg + 2;
+  acc.n2 = n2; acc.K2 = g.K2; acc.N1 = g.N1; acc.lo1 = g.lo1; acc.lo2 = g.lo2;
+  acc.hi1 = g.lo1 + g.N1 - 1; acc.hi2 = g.lo2 + g.N2 - 1;
+  acc.yderiv = set == 1;
+  for (int it = threadIdx.x; it < nc * B; it += NT) {
+    const int bb = it / nc, q = it - bb * nc;
+    ColSpecGlobal<T> c = acc;
+    c.kx = c0 + q;
+    c.col = ws + 2 * q;
+    fft4_dispatch<true, 1, T>(n2, c, bb, tw2);
+  }
+  __syncthreads();
+  T *db = a.cols + ((int64_t)lc * nset + set) * n2 * per * 2;
+  for (int it = threadIdx.x; it < nc * A; it += NT) {
+    const int k1 = it / nc, q = it - k1 * nc;
+    const T *col = ws + 2 * q;
+    switch (n2) {
+      case 16: col_step2_band<4, 4, T>(col, acc.cpitch, k1, n2, db, per, c0 + q, n2, 0); break;
+      case 32: col_step2_band<8, 4, T>(col, acc.cpitch, k1, n2, db, per, c0 + q, n2, 0); break;
+      case 64: col_step2_band<8, 8, T>(col, acc.cpitch, k1, n2, db, per, c0 + q, n2, 0); break;
+      default: col_step2_band<16, 8, T>(col, acc.cpitch, k1, n2, db, per, c0 + q, n2, 0); break;
+    }
+  }
+}
+
+constexpr int ADJ_QCAP = 128;   // per-wave queue of the band's points (entries)
+
+// LDS of a band item: the grid planes (three for the gradients: rows of
+// interleaved (u, du/dx) and rows of du/dy; one, of u, for the FP64 reconstruction),
+// the row twiddles and the per-wave queues of the band's points.
+struct BandLayout {
+  int rows;       // band rows including halo = band_rows + W, even
+  int apitch;     // grid row pitch (elements) = n1 + W - 1, rounded up to even: the first W - 1
+                  // columns are repeated after the last, so a footprint's W columns are contiguous
+  size_t gy_off, tw_off;   // element offsets
+  size_t q_off, total;     // bytes
+};
+
+__host__ __device__ inline BandLayout band_layout(const Geom &g, int W, int band_rows, size_t elem, bool recon,
+                                                  int threads) {
+  BandLayout L;
+  L.rows = band_rows + W;
+  L.apitch = (g.n1 + W - 1 + 1) & ~1;
+  const size_t gsz = (size_t)L.rows * L.apitch;
+  L.gy_off = 2 * gsz;
+  L.tw_off = (recon ? 1 : 3) * gsz;
+  L.q_off = (L.tw_off + 2 * (size_t)g.n1) * elem;
+  // a band that is the whole grid serves every point and queues none
+  L.total = L.q_off + (band_rows < g.n2 ? (size_t)(threads / 64) * ADJ_QCAP * sizeof(int) : 0);
+  return L;
+}
+
+// Gradients at one point whose footprint starts in band row r0, from the band's
+// three grids (W x W taps each); the chain rule through the strength
+// c_j = w_j W(x_j) h_j turns the interpolated u, du/dx, du/dy into dL/dh,
+// dL/dx, dL/dy.
+//
+// RECON: the reconstruction mode.  Only u is interpolated; it is the truncated
+// series h_rec(x_j) (the plan's scale is not applied in this mode), stored to
+// grad_h when given, and the point adds (t - h_rec)^2, t^2 and w t^2 to acc, with
+// t = W(x_j) h_j the windowed height.
+//
+// POLY: the taps are the plan's polynomials (FP32 up to W = 8, FP64), taken in
+// mirror pairs; otherwise psi itself.  Either is fixed at compile time (a
+// run-time choice makes the compiler keep the taps in scratch).
+template <typename T, int W, bool POLY, bool RECON>
+__device__ __forceinline__ void gather_point(const AdjArgs<T> &a, const T *G, const T *Gy, int apitch, int r0,
+                                             const FineCoord<T> &fy, int64_t j, T xj, T yj, T hj, T wj, T cx, T cy,
+                                             T R, T pr, double (&acc)[3]) {
+  const Geom &g = a.g;
+  const T halfw = T(W) / T(2);
+  const FineCoord<T> fx = fine_coord<T>(xj, a.s1_hi, a.s1_lo, halfw);
+  T kx[W];
+  T u = 0, ux = 0, uy = 0;
+  using V2 = typename vec2<T>::type;
+  // rows in natural column order with the wrap-around columns repeated: the
+  // W taps of a row are W consecutive elements from one base address
+  const int e0 = r0 * apitch + (fx.i0 & (g.n1 - 1));
+  const V2 *puv = reinterpret_cast<const V2 *>(G) + e0;
+  const T *p1 = (RECON ? G : Gy) + e0;
+  auto row = [&](int dy, T kyv) {
+    T su = 0, sx = 0, sy = 0;
+    const V2 *q = puv + dy * apitch;
+    const T *qy = p1 + dy * apitch;
+#pragma unroll
+    for (int dx = 0; dx < W; ++dx) {
+      if constexpr (RECON) {
+        su += kx[dx] * qy[dx];
+      } else {
+        const V2 v = q[dx];
+        su += kx[dx] * v.x;
+        sx += kx[dx] * v.y;
+        sy += kx[dx] * qy[dx];
+      }
+    }
+    u += kyv * su;
+    if constexpr (!RECON) {
+      ux += kyv * sx;
+      uy += kyv * sy;
+    }
+  };
+  if constexpr (POLY && sizeof(T) == 8) {
+    es_taps_poly64<W>(tap_u64(fx, double(W) * 0.5), a.es64, kx);
+    const double uyv = tap_u64(fy, double(W) * 0.5), sy2 = uyv * uyv;
+    // two rows at a time, so the loads of all W rows are not held in registers together
+#pragma unroll 1
+    for (int d = 0; d < W / 2; ++d) {
+      double ta, tb;
+      poly64_pair_eval(poly64_pair(a.es64, d), uyv, sy2, ta, tb);
+      row(d, ta);
+      row(W - 1 - d, tb);
+    }
+  } else if constexpr (POLY) {
+    T ky[W];
+    es_taps_poly<W>(fx, float(W) * 0.5f, a.es, kx);
+    es_taps_poly<W>(fy, float(W) * 0.5f, a.es, ky);
+#pragma unroll
+    for (int dy = 0; dy < W; ++dy) row(dy, ky[dy]);
+  } else {
+    const T zsc = T(2) / T(W);
+#pragma unroll
+    for (int d = 0; d < W; ++d) kx[d] = ker_eval(fx.offset(d) * zsc, a.beta);
+    // one row at a time, so the loads of all W rows are not hoisted together
+#pragma unroll 1
+    for (int dy = 0; dy < W; ++dy) row(dy, ker_eval(fy.offset(dy) * zsc, a.beta));
+  }
+  if constexpr (RECON) {
+    const double t = (double)(hj * hann_w(a.window_kind, xj, yj, cx, cy, R, pr));
+    const double d = t - (double)u;
+    acc[0] += d * d;
+    acc[1] += t * t;
+    acc[2] += (double)wj * t * t;
+    if (a.grad_h) a.grad_h[j] = u;
+    return;
+  }
+  T dWx, dWy;
+  const T Wv = hann_wg(a.window_kind, xj, yj, cx, cy, R, pr, dWx, dWy);
+  if (a.grad_h) a.grad_h[j] = wj * Wv * u;
+  if (a.grad_x || a.grad_y) {
+    const T wh = wj * hj;
+    if (a.grad_x) a.grad_x[j] = wh * (dWx * u + Wv * ux);
+    if (a.grad_y) a.grad_y[j] = wh * (dWy * u + Wv * uy);
+  }
+}
+
+// All points of one item.  When the band is the whole grid every point is
+// served: wave w takes blocks of 64 consecutive points, one per lane, each lane's
+// next point loaded while the current one is gathered.  Otherwise every y of the
+// item is read and the points of the band are queued per wave and gathered 64 at
+// a time: served where they stand, only one lane in `bands` would be active for
+// points in no spatial order, at the cost of a whole wave's gather each time.
+template <typename T, int W, int NT, bool POLY, bool RECON>
+__device__ __forceinline__ void gather_item(const AdjArgs<T> &a, const T *G, const T *Gy, int apitch, int *queue,
+                                            int band_lo, int64_t begin, int64_t end, T cx, T cy, T R,
+                                            double (&acc)[3]) {
+  const T pr = R > T(0) ? T(M_PI) / R : T(0);
+  const T halfw = T(W) / T(2);
+  constexpr int NWV = NT / 64;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int mask2 = a.g.n2 - 1;
+  if (begin >= end) return;
+  if (a.band_rows > mask2) {
+    struct Pt {
+      T x, y, h, w;
+    };
+    auto load = [&](Pt &b, int64_t i) {
+      const int64_t ic = i < end ? i : end - 1;   // past the end: re-read the last point (unused)
+      b.x = a.x[ic]; b.y = a.y[ic]; b.h = a.h[ic]; b.w = a.w[ic];
+    };
+    auto step = [&](const Pt &b, int64_t i) {
+      if (i < end) {
+        const FineCoord<T> fy = fine_coord<T>(b.y, a.s2_hi, a.s2_lo, halfw);
+        gather_point<T, W, POLY, RECON>(a, G, Gy, apitch, fy.i0 & mask2, fy, i, b.x, b.y, b.h, b.w, cx, cy, R, pr,
+                                        acc);
+      }
+    };
+    const int64_t stride = (int64_t)NWV * 64;
+    int64_t i = begin + (int64_t)wave * 64 + lane;
+    Pt b0, b1;
+    load(b0, i);
+    for (; i - lane < end; i += 2 * stride) {
+      load(b1, i + stride);
+      step(b0, i);
+      load(b0, i + 2 * stride);
+      step(b1, i + stride);
+    }
+    return;
+  }
+  constexpr int U = 4, BLK = 64 * U;
+  int *wq = queue + wave * ADJ_QCAP;
+  auto drain = [&](int n) {
+    if (lane < n) {
+      const int64_t j = begin + wq[lane];
+      const T xj = a.x[j], yj = a.y[j], hj = a.h[j], wj = a.w[j];
+      const FineCoord<T> fy = fine_coord<T>(yj, a.s2_hi, a.s2_lo, halfw);
+      gather_point<T, W, POLY, RECON>(a, G, Gy, apitch, (fy.i0 & mask2) - band_lo, fy, j, xj, yj, hj, wj, cx, cy, R,
+                                      pr, acc);
+    }
+  };
+  auto order = [] {   // a wave's LDS accesses complete in issue order; keep the compiler to it
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  };
+  int nq = 0;   // queued points (the same in every lane)
+  T yb[U];
+  auto load = [&](int64_t p) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int64_t i = p + u * 64 + lane;
+      yb[u] = a.y[i < end ? i : end - 1];
+    }
+  };
+  int64_t p = begin + (int64_t)wave * BLK;
+  load(p);
+  for (; p < end; p += (int64_t)NWV * BLK) {
+    bool in[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int r0 = (fine_coord<T>(yb[u], a.s2_hi, a.s2_lo, halfw).i0 & mask2) - band_lo;
+      in[u] = p + u * 64 + lane < end && r0 >= 0 && r0 < a.band_rows;
+    }
+    load(p + (int64_t)NWV * BLK);
+#pragma unroll 1
+    for (int u = 0; u < U; ++u) {
+      const bool on = u == 0 ? in[0] : u == 1 ? in[1] : u == 2 ? in[2] : in[3];
+      const uint64_t m = __ballot(on);
+      if (m == 0) continue;
+      if (on) {
+        const int pos = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+        wq[nq + pos] = (int)(p + u * 64 + lane - begin);   // nq < 64 here, so nq + pos < ADJ_QCAP
+      }
+      nq += __popcll(m);
+      if (nq >= 64) {
+        order();
+        drain(64);
+        nq -= 64;
+        const int rest = lane < nq ? wq[64 + lane] : 0;
+        order();
+        if (lane < nq) wq[lane] = rest;
+        order();
+      }
+    }
+  }
+  order();
+  drain(nq);
+}
+
+template <typename T, int W, int NT, bool POLY, bool RECON>
+__global__ __launch_bounds__(NT) void adj_kernel(AdjArgs<T> a) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  T *sm = reinterpret_cast<T *>(smem_raw);
+  __shared__ int s_item;
+  const Geom &g = a.g;
+  const BandLayout L = band_layout(g, W, a.band_rows, sizeof(T), RECON, NT);
+  const int pitch = L.apitch;
+  // gradients: rows of (u, du/dx) pairs (the real and imaginary parts of one
+  // complex row transform, kept interleaved) in G, rows of du/dy in Gy;
+  // reconstruction: rows of u in G
+  T *G = sm, *Gy = sm + L.gy_off, *tw1 = sm + L.tw_off;
+  int *queue = reinterpret_cast<int *>(smem_raw + L.q_off);
+  const int per = g.K1 + 1, n1 = g.n1, n2 = g.n2, K1 = g.K1;
+  // the transforms' twiddles stay in LDS for all items of this workgroup (the
+  // barrier at the top of the item loop orders them before first use)
+  for (int i = threadIdx.x; i < 2 * n1; i += NT) tw1[i] = a.tw1[i];
+  for (;;) {
+    if (threadIdx.x == 0) s_item = atomicAdd(a.work_counter, 1);
+    __syncthreads();
+    const int64_t idx = s_item;
+    __syncthreads();
+    if (idx >= a.n_items) break;
+    const AdjItem it = a.items[idx];
+    const int y0 = it.band * a.band_rows;   // fine row of band-local row 0
+    const size_t set = (size_t)n2 * per * 2;
+    const T *db0 = a.cols + (size_t)(it.cell - a.cell0) * (RECON ? 1 : 2) * set, *db1 = db0 + set;
+    // Row stage, one batch of inverse transforms: the (u, du/dx) rows, spectrum
+    // Z(k) = D(k) + i (i k D(k)) = (1 - k) D(k), stored interleaved in G, and
+    // the du/dy row pairs, Z(k) = Dy_r(k) + i Dy_r+1(k), in Gy (RECON: row pairs of
+    // u); the bins k < 0 are the conjugates of column -k.  The first step reads
+    // the spectra from the cell's column data in global memory, the second writes
+    // natural column order with the wrap-around columns; band rows = band_rows +
+    // W and y0 are even, so the rows pair up exactly.
+    const int nuv = RECON ? 0 : L.rows;
+    row_ifft_natural<NT, T>(
+        n1, nuv + L.rows / 2, tw1, W - 1,
+        [&](int q) {
+          RowSpecAcc<T> acc;
+          const int r = q < nuv ? q : 2 * (q - nuv);
+          acc.db = RECON || q < nuv ? db0 : db1;
+          acc.row = (y0 + r) & (n2 - 1);
+          acc.pair = q >= nuv;
+          acc.per = per;
+          acc.n1 = n1;
+          acc.K1 = K1;
+          acc.r0 = q < nuv ? G + 2 * r * pitch : (RECON ? G : Gy) + r * pitch;
+          acc.r1 = q < nuv ? acc.r0 + 1 : acc.r0 + pitch;
+          acc.stride = q < nuv ? 2 : 1;
+          return acc;
+        },
+        [&](int q) {
+          StridedPairAcc<T> acc;
+          const int r = q < nuv ? q : 2 * (q - nuv);
+          acc.r0 = q < nuv ? G + 2 * r * pitch : (RECON ? G : Gy) + r * pitch;
+          acc.r1 = q < nuv ? acc.r0 + 1 : acc.r0 + pitch;
+          acc.stride = q < nuv ? 2 : 1;
+          return acc;
+        });
+
+    // Gather at the points of this band.
+    const double *wn = a.windows + 3 * (int64_t)it.cell;
+    double acc[3] = {0.0, 0.0, 0.0};
+    gather_item<T, W, NT, POLY, RECON>(a, G, Gy, pitch, queue, y0, it.begin, it.end, T(wn[0]), T(wn[1]), T(wn[2]),
+                                       acc);
+    if constexpr (RECON) {
+      // the item's three sums, reduced in a fixed order (waves, then lanes)
+      __syncthreads();
+      double *red = reinterpret_cast<double *>(sm);
+      for (int k = 0; k < 3; ++k) {
+        double v = acc[k];
+        for (int o = 32; o > 0; o >>= 1) v += __shfl_down(v, o, 64);
+        if ((threadIdx.x & 63) == 0) red[k * (NT / 64) + (threadIdx.x >> 6)] = v;
+      }
+      __syncthreads();
+      if (threadIdx.x < 3) {
+        double v = 0.0;
+        for (int q = 0; q < NT / 64; ++q) v += red[threadIdx.x * (NT / 64) + q];
+        a.rec_part[3 * idx + threadIdx.x] = v;
+      }
+    }
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) {
+    __threadfence();
+    const int old = atomicAdd(a.done_counter, 1);
+    if (old == (int)gridDim.x - 1) {
+      *a.work_counter = 0;
+      *a.done_counter = 0;
+    }
+  }
+}
+
+constexpr int ADJ_THREADS = 512;
+
+// Compiled with polynomial taps for FP32 (W <= ES_MAXW) and FP64, and with the exact
+// kernel; the reconstruction in FP64 (FP32: rec_kernel below).
+template <typename T, int W>
+static const void *adj_fn(bool poly, bool recon) {
+  if constexpr (sizeof(T) == 8) {
+    if (recon)
+      return poly ? (const void *)&adj_kernel<T, W, ADJ_THREADS, true, true>
+                  : (const void *)&adj_kernel<T, W, ADJ_THREADS, false, true>;
+  }
+  if constexpr (sizeof(T) == 8 || W <= ES_MAXW) {
+    if (poly) return (const void *)&adj_kernel<T, W, ADJ_THREADS, true, false>;
+  }
+  return recon ? nullptr : (const void *)&adj_kernel<T, W, ADJ_THREADS, false, false>;
+}
+
+template <typename T>
+static const void *adj_fn_w(int W, bool poly, bool recon) {
+  switch (W) {
+    case 4: return adj_fn<T, 4>(poly, recon);
+    case 6: return adj_fn<T, 6>(poly, recon);
+    case 8: return adj_fn<T, 8>(poly, recon);
+    case 10: return adj_fn<T, 10>(poly, recon);
+    case 12: return adj_fn<T, 12>(poly, recon);
+    case 14: return adj_fn<T, 14>(poly, recon);
+    case 16: return adj_fn<T, 16>(poly, recon);
+    default: return nullptr;
+  }
+}
+
+// ------------------------------------------------------------------ FP32 reconstruction
+//
+// FP32 plans reconstruct from rows of (u, du/dx) like the gradients' (the imaginary
+// half unused), in row bands that transform their own columns.  The per-cell sums of
+// squared residuals are FP64 sums of FP32 residuals, so they follow every rounding
+// of u: the pairing of rows that serves FP64 above changes them by about 5e-8.
+
+struct RecLayout {
+  int rows;       // band rows including halo = band_rows + W
+  int apitch;     // grid row pitch (elements), as BandLayout
+  int cpitch;     // column-workspace pitch (elements) = 2 (K1 + 1) + 2
+  size_t db_off, ws_off, st_off;   // element offsets (the grid of (u, du/dx) pairs at 0)
+  size_t tw_off;  // twiddles of the row (n1) and column (n2) transforms, interleaved complex
+  size_t total;   // elements
+};
+
+__host__ __device__ inline RecLayout rec_layout(const Geom &g, int W, int band_rows, size_t elem) {
+  RecLayout L;
+  L.rows = band_rows + W;
+  L.apitch = (g.n1 + W - 1 + 1) & ~1;
+  L.cpitch = 2 * (g.K1 + 1) + 2;
+  const size_t gsz = 2 * (size_t)L.rows * L.apitch;
+  // the column workspace and the staging area behind it alias the grid (they
+  // are dead before it is written) but never the band spectra, which are filled
+  // while they are live
+  const size_t ws = (size_t)g.n2 * L.cpitch;
+  L.ws_off = 0;
+  L.st_off = ws;
+  L.db_off = std::max(gsz, ws + adj_stage_elems(g, elem));
+  L.tw_off = L.db_off + (size_t)L.rows * (g.K1 + 1) * 2;
+  L.total = L.tw_off + 2 * (size_t)(g.n1 + g.n2);
+  return L;
+}
+
+// First-step accessor of its row transforms: bin k of the row's spectrum (1 - k) D(k)
+// from the band's column data db ([row][kx] complex).
+template <typename T>
+struct RecSpecAcc {
   const T *db;
   T *r0, *r1;
   int stride, row, per, n1, K1;
@@ -310,19 +800,12 @@ struct RowSpecAcc {
   }
 };
 
-// Gradients at one point from the band's three grids (W x W taps each), if the
-// point's footprint starts in this band; the chain rule through the strength
-// c_j = w_j W(x_j) h_j turns the interpolated u, du/dx, du/dy into dL/dh,
-// dL/dx, dL/dy.
-//
-// RECON: the reconstruction mode.  Only u is interpolated (from the u half of
-// Guv); it is the truncated series h_rec(x_j) (the plan's scale is not applied in
-// this mode), stored to grad_h when given, and the point adds (t - h_rec)^2, t^2
-// and w t^2 to acc, with t = W(x_j) h_j the windowed height.
-template <typename T, int W, bool POLY, bool RECON>
-__device__ __forceinline__ void gather_point(const AdjArgs<T> &a, const T *Guv, const T *Gy, int apitch,
-                                             int band_lo, int64_t j, T xj, T yj, T hj, T wj, T cx, T cy, T R,
-                                             T pr, double (&acc)[3]) {
+// The truncated series at one point, if the point's footprint starts in this band.
+template <int W, bool POLY>
+__device__ __forceinline__ void rec_point(const AdjArgs<float> &a, const float *Guv, int apitch, int band_lo,
+                                          int64_t j, float xj, float yj, float hj, float wj, float cx, float cy,
+                                          float R, float pr, double (&acc)[3]) {
+  using T = float;
   const Geom &g = a.g;
   const T halfw = T(W) / T(2);
   const FineCoord<T> fy = fine_coord<T>(yj, a.s2_hi, a.s2_lo, halfw);
@@ -330,36 +813,15 @@ __device__ __forceinline__ void gather_point(const AdjArgs<T> &a, const T *Guv, 
   if (r0 < 0 || r0 >= a.band_rows) return;
   const FineCoord<T> fx = fine_coord<T>(xj, a.s1_hi, a.s1_lo, halfw);
   T kx[W];
-  T u = 0, ux = 0, uy = 0;
-  // rows in natural column order with the wrap-around columns repeated: the
-  // W taps of a row are W consecutive elements from one base address
-  using V2 = typename vec2<T>::type;
-  const int e0 = r0 * apitch + (fx.i0 & (g.n1 - 1));
-  const V2 *puv = reinterpret_cast<const V2 *>(Guv) + e0;
-  const T *py = Gy + e0;
+  T u = 0;
+  const float2 *puv = reinterpret_cast<const float2 *>(Guv) + r0 * apitch + (fx.i0 & (g.n1 - 1));
   auto row = [&](T kyv) {
-    T su = 0, sx = 0, sy = 0;
+    T su = 0;
 #pragma unroll
-    for (int dx = 0; dx < W; ++dx) {
-      const V2 v = puv[dx];
-      su += kx[dx] * v.x;
-      if constexpr (!RECON) {
-        sx += kx[dx] * v.y;
-        sy += kx[dx] * py[dx];
-      }
-    }
+    for (int dx = 0; dx < W; ++dx) su += kx[dx] * puv[dx].x;
     u += kyv * su;
-    if constexpr (!RECON) {
-      ux += kyv * sx;
-      uy += kyv * sy;
-    }
     puv += apitch;
-    py += apitch;
   };
-  // kernel values: the plan's per-tap polynomials (FP32, W <= ES_MAXW) or psi
-  // itself, chosen at compile time (a run-time choice makes the compiler keep
-  // the taps in scratch); the exact kernel goes one row at a time, so the
-  // loads of all W rows are not hoisted into registers together
   if constexpr (POLY) {
     T ky[W];
     es_taps_poly<W>(fx, float(W) * 0.5f, a.es, kx);
@@ -373,43 +835,27 @@ __device__ __forceinline__ void gather_point(const AdjArgs<T> &a, const T *Guv, 
 #pragma unroll 1
     for (int dy = 0; dy < W; ++dy) row(ker_eval(fy.offset(dy) * zsc, a.beta));
   }
-  if constexpr (RECON) {
-    const double t = (double)(hj * hann_w(a.window_kind, xj, yj, cx, cy, R, pr));
-    const double d = t - (double)u;
-    acc[0] += d * d;
-    acc[1] += t * t;
-    acc[2] += (double)wj * t * t;
-    if (a.grad_h) a.grad_h[j] = u;
-    return;
-  }
-  T dWx, dWy;
-  const T Wv = hann_wg(a.window_kind, xj, yj, cx, cy, R, pr, dWx, dWy);
-  if (a.grad_h) a.grad_h[j] = wj * Wv * u;
-  if (a.grad_x || a.grad_y) {
-    const T wh = wj * hj;
-    if (a.grad_x) a.grad_x[j] = wh * (dWx * u + Wv * ux);
-    if (a.grad_y) a.grad_y[j] = wh * (dWy * u + Wv * uy);
-  }
+  const double t = (double)(hj * hann_w(a.window_kind, xj, yj, cx, cy, R, pr));
+  const double d = t - (double)u;
+  acc[0] += d * d;
+  acc[1] += t * t;
+  acc[2] += (double)wj * t * t;
+  if (a.grad_h) a.grad_h[j] = u;
 }
 
 // All points of one item; every point is read (its band decides whether it is
 // served).  Wave w takes blocks of 256 consecutive points and lane l gathers
-// points l, l + 64, l + 128 and l + 192 of a block, so at every step the 64
-// lanes work on 64 consecutive points: for points stored in raster order their
-// footprints overlap, many lanes read the same LDS words (one broadcast) and
-// the others fall on neighbouring banks.  (Runs of 4 consecutive points per
-// lane put the lanes 4 points apart, and about half of the LDS time went to
-// bank conflicts.)  The loads run two blocks ahead in three register buffers,
-// so the gather is not serialised behind point loads; each wave load reads 256
-// contiguous bytes of an array.  FP64 and the wider kernels (register budget)
-// take one point per thread and step.
-template <typename T, int W, int NT, bool POLY, bool RECON>
-__device__ __forceinline__ void gather_item(const AdjArgs<T> &a, const T *Guv, const T *Gy, int apitch,
-                                            int band_lo, int64_t begin, int64_t end, T cx, T cy, T R,
-                                            double (&acc)[3]) {
+// points l, l + 64, l + 128 and l + 192 of a block, so at every step the 64 lanes
+// work on 64 consecutive points (overlapping footprints in raster order).  The
+// loads run two blocks ahead in three register buffers.  The wider kernels
+// (register budget) take one point per thread and step.
+template <int W, int NT, bool POLY>
+__device__ __forceinline__ void rec_item(const AdjArgs<float> &a, const float *Guv, int apitch, int band_lo,
+                                         int64_t begin, int64_t end, float cx, float cy, float R,
+                                         double (&acc)[3]) {
+  using T = float;
   const T pr = R > T(0) ? T(M_PI) / R : T(0);
-  constexpr bool kBlocks = sizeof(T) == 4 && W <= 6;
-  if constexpr (kBlocks) {
+  if constexpr (W <= 6) {
     constexpr int U = 4, BLK = 64 * U, NWV = NT / 64;
     struct Pts {
       T x[U], y[U], h[U], w[U];
@@ -429,8 +875,7 @@ __device__ __forceinline__ void gather_item(const AdjArgs<T> &a, const T *Guv, c
       for (int u = 0; u < U; ++u) {
         const int64_t i = pb + u * 64 + lane;
         if (i < end)
-          gather_point<T, W, POLY, RECON>(a, Guv, Gy, apitch, band_lo, i, b.x[u], b.y[u], b.h[u], b.w[u], cx, cy,
-                                          R, pr, acc);
+          rec_point<W, POLY>(a, Guv, apitch, band_lo, i, b.x[u], b.y[u], b.h[u], b.w[u], cx, cy, R, pr, acc);
       }
     };
     if (begin < end) {
@@ -449,67 +894,50 @@ __device__ __forceinline__ void gather_item(const AdjArgs<T> &a, const T *Guv, c
     }
   } else {
     for (int64_t j = begin + threadIdx.x; j < end; j += NT)
-      gather_point<T, W, POLY, RECON>(a, Guv, Gy, apitch, band_lo, j, a.x[j], a.y[j], a.h[j], a.w[j], cx, cy, R,
-                                      pr, acc);
+      rec_point<W, POLY>(a, Guv, apitch, band_lo, j, a.x[j], a.y[j], a.h[j], a.w[j], cx, cy, R, pr, acc);
   }
 }
 
-template <typename T, int W, int NT, bool POLY, bool RECON>
-__global__ __launch_bounds__(NT) void adj_kernel(AdjArgs<T> a) {
+template <int W, bool POLY>
+__global__ __launch_bounds__(ADJ_THREADS) void rec_kernel(AdjArgs<float> a) {
+  using T = float;
+  constexpr int NT = ADJ_THREADS;
   extern __shared__ __align__(16) unsigned char smem_raw[];
   T *sm = reinterpret_cast<T *>(smem_raw);
   __shared__ int s_item;
   const Geom &g = a.g;
-  const AdjLayout L = adj_layout(g, W, a.band_rows, sizeof(T));
+  const RecLayout L = rec_layout(g, W, a.band_rows, sizeof(T));
   const int pitch = L.apitch;
-  // Guv: rows of (u, du/dx) pairs (the real and imaginary parts of one complex
-  // row transform, kept interleaved); Gy: rows of du/dy
-  T *Guv = sm + L.g_off, *Gy = sm + L.gy_off;
-  T *db0 = sm + L.db0_off, *db1 = sm + L.db1_off, *ws = sm + L.ws_off;
+  T *Guv = sm;   // rows of (u, du/dx) pairs, interleaved
+  T *db = sm + L.db_off, *ws = sm + L.ws_off;
   const int per = g.K1 + 1;
-  const bool persistent = a.work_counter != nullptr;
-  int64_t idx = a.item_base + blockIdx.x;
-  if (!persistent && idx >= a.n_items) return;
   // the transforms' twiddles stay in LDS for all items of this workgroup (the
   // barrier at the top of the item loop orders them before first use)
   T *tw1 = sm + L.tw_off, *tw2 = tw1 + 2 * g.n1;
   for (int i = threadIdx.x; i < 2 * g.n1; i += NT) tw1[i] = a.tw1[i];
   for (int i = threadIdx.x; i < 2 * g.n2; i += NT) tw2[i] = a.tw2[i];
-  if (!persistent) __syncthreads();
   for (;;) {
-    if (persistent) {
-      if (threadIdx.x == 0) s_item = atomicAdd(a.work_counter, 1);
-      __syncthreads();
-      idx = s_item;
-      __syncthreads();
-      if (idx >= a.n_items) break;
-    }
+    if (threadIdx.x == 0) s_item = atomicAdd(a.work_counter, 1);
+    __syncthreads();
+    const int64_t idx = s_item;
+    __syncthreads();
+    if (idx >= a.n_items) break;
     const AdjItem it = a.items[idx];
     const T *gc = a.fbar + (int64_t)it.cell * g.N1 * g.N2 * 2;
     const int y0 = it.band * a.band_rows;   // fine row of band-local row 0
-
-    // columns of H and of i ky H, inverse transformed along y; keep the band rows
     T *st = sm + L.st_off;
-    const T two_lam = RECON ? T(1) : a.keep ? T(2.0 * (a.lam ? a.lam[it.cell] : 1.0)) : T(1);
     stage_spectrum<T, NT>(a, gc, it.cell, st);
-    for (int pass = 0; pass < (RECON ? 1 : 2); ++pass)
-      column_pass<T, NT>(a, st, tw2, two_lam, ws, L.cpitch, pass == 1, pass == 0 ? db0 : db1, L.rows, y0);
-
-    // Row stage, one batch of inverse transforms: the (u, du/dx) rows, spectrum
-    // Z(k) = D(k) + i (i k D(k)) = (1 - k) D(k), stored interleaved in Guv, and
-    // the du/dy row pairs, Z(k) = Dy_r(k) + i Dy_r+1(k), in Gy; the bins k < 0
-    // are the conjugates of column -k.  The first step of the transform reads
-    // the spectra straight from the band's column data (no separate pass
-    // writing them into the grids), the second writes natural column order with
-    // the wrap-around columns; band rows = band_rows + W is even, so the du/dy
-    // rows pair up exactly.
+    column_pass<T, NT>(a, st, tw2, T(1), ws, L.cpitch, false, db, L.rows, y0);
+    // the (u, du/dx) rows, spectrum (1 - k) D(k)
+    float *db0 = db, *db1 = db, *Gy = Guv;
+    constexpr bool RECON = true;
     const int n1 = g.n1;
     const int ny_pairs = L.rows / 2;
     const int K1 = g.K1;
     row_ifft_natural<NT, T>(
         n1, RECON ? L.rows : L.rows + ny_pairs, tw1, W - 1,
         [&](int q) {
-          RowSpecAcc<T> acc;
+          RecSpecAcc<T> acc;
           acc.db = q < L.rows ? db0 : db1;
           acc.row = q < L.rows ? q : 2 * (q - L.rows);
           acc.pair = q >= L.rows;
@@ -541,31 +969,26 @@ __global__ __launch_bounds__(NT) void adj_kernel(AdjArgs<T> a) {
           return acc;
         });
 
-    // Gather at the points of this band.
     const double *wn = a.windows + 3 * (int64_t)it.cell;
     double acc[3] = {0.0, 0.0, 0.0};
-    gather_item<T, W, NT, POLY, RECON>(a, Guv, Gy, L.apitch, it.band * a.band_rows, it.begin, it.end, T(wn[0]),
-                                       T(wn[1]), T(wn[2]), acc);
-    if constexpr (RECON) {
-      // the item's three sums, reduced in a fixed order (waves, then lanes)
-      __syncthreads();
-      double *red = reinterpret_cast<double *>(sm);
-      for (int k = 0; k < 3; ++k) {
-        double v = acc[k];
-        for (int o = 32; o > 0; o >>= 1) v += __shfl_down(v, o, 64);
-        if ((threadIdx.x & 63) == 0) red[k * (NT / 64) + (threadIdx.x >> 6)] = v;
-      }
-      __syncthreads();
-      if (threadIdx.x < 3) {
-        double v = 0.0;
-        for (int q = 0; q < NT / 64; ++q) v += red[threadIdx.x * (NT / 64) + q];
-        a.rec_part[3 * idx + threadIdx.x] = v;
-      }
+    rec_item<W, NT, POLY>(a, Guv, pitch, y0, it.begin, it.end, T(wn[0]), T(wn[1]), T(wn[2]), acc);
+    // the item's three sums, reduced in a fixed order (waves, then lanes)
+    __syncthreads();
+    double *red = reinterpret_cast<double *>(sm);
+    for (int k = 0; k < 3; ++k) {
+      double v = acc[k];
+      for (int o = 32; o > 0; o >>= 1) v += __shfl_down(v, o, 64);
+      if ((threadIdx.x & 63) == 0) red[k * (NT / 64) + (threadIdx.x >> 6)] = v;
     }
     __syncthreads();
-    if (!persistent) break;
+    if (threadIdx.x < 3) {
+      double v = 0.0;
+      for (int q = 0; q < NT / 64; ++q) v += red[threadIdx.x * (NT / 64) + q];
+      a.rec_part[3 * idx + threadIdx.x] = v;
+    }
+    __syncthreads();
   }
-  if (persistent && threadIdx.x == 0) {
+  if (threadIdx.x == 0) {
     __threadfence();
     const int old = atomicAdd(a.done_counter, 1);
     if (old == (int)gridDim.x - 1) {
@@ -575,57 +998,26 @@ __global__ __launch_bounds__(NT) void adj_kernel(AdjArgs<T> a) {
   }
 }
 
-// Compiled with the polynomial taps for FP32 plans that carry them (W <= ES_MAXW).
-template <typename T, int W>
-constexpr bool adj_has_poly() { return sizeof(T) == 4 && W <= ES_MAXW; }
-
-template <typename T, int W>
-static const void *adj_fn(int threads, bool poly) {
-  if constexpr (adj_has_poly<T, W>()) {
-    if (poly)
-      return threads == 256 ? (const void *)&adj_kernel<T, W, 256, true, false>
-                            : (const void *)&adj_kernel<T, W, 512, true, false>;
+template <int W>
+static const void *rec_fn_w(bool poly) {
+  if constexpr (W <= ES_MAXW) {
+    if (poly) return (const void *)&rec_kernel<W, true>;
   }
-  return threads == 256 ? (const void *)&adj_kernel<T, W, 256, false, false>
-                        : (const void *)&adj_kernel<T, W, 512, false, false>;
+  return (const void *)&rec_kernel<W, false>;
 }
 
-template <typename T, int W, bool RECON>
-static hipError_t launch_adj_w(const AdjArgs<T> &a, int blocks, int threads, size_t lds, hipStream_t s) {
-  if constexpr (adj_has_poly<T, W>()) {
-    if (a.es.on) {
-      if (threads == 256) hipLaunchKernelGGL((adj_kernel<T, W, 256, true, RECON>), dim3(blocks), dim3(256), lds, s, a);
-      else hipLaunchKernelGGL((adj_kernel<T, W, 512, true, RECON>), dim3(blocks), dim3(512), lds, s, a);
-      return hipGetLastError();
-    }
-  }
-  if (threads == 256) hipLaunchKernelGGL((adj_kernel<T, W, 256, false, RECON>), dim3(blocks), dim3(256), lds, s, a);
-  else hipLaunchKernelGGL((adj_kernel<T, W, 512, false, RECON>), dim3(blocks), dim3(512), lds, s, a);
-  return hipGetLastError();
-}
-
-template <typename T, bool RECON>
-static hipError_t launch_adj_mode(const AdjArgs<T> &a, int W, int blocks, int threads, size_t lds, hipStream_t s) {
+static const void *rec_fn(int W, bool poly) {
   switch (W) {
-    case 4: return launch_adj_w<T, 4, RECON>(a, blocks, threads, lds, s);
-    case 6: return launch_adj_w<T, 6, RECON>(a, blocks, threads, lds, s);
-    case 8: return launch_adj_w<T, 8, RECON>(a, blocks, threads, lds, s);
-    case 10: return launch_adj_w<T, 10, RECON>(a, blocks, threads, lds, s);
-    case 12: return launch_adj_w<T, 12, RECON>(a, blocks, threads, lds, s);
-    case 14: return launch_adj_w<T, 14, RECON>(a, blocks, threads, lds, s);
-    case 16: return launch_adj_w<T, 16, RECON>(a, blocks, threads, lds, s);
-    default: return hipErrorInvalidValue;
+    case 4: return rec_fn_w<4>(poly);
+    case 6: return rec_fn_w<6>(poly);
+    case 8: return rec_fn_w<8>(poly);
+    case 10: return rec_fn_w<10>(poly);
+    case 12: return rec_fn_w<12>(poly);
+    case 14: return rec_fn_w<14>(poly);
+    case 16: return rec_fn_w<16>(poly);
+    default: return nullptr;
   }
 }
-
-template <typename T>
-hipError_t launch_adj(const AdjArgs<T> &a, int W, int blocks, int threads, size_t lds, hipStream_t s) {
-  return a.rec_part ? launch_adj_mode<T, true>(a, W, blocks, threads, lds, s)
-                    : launch_adj_mode<T, false>(a, W, blocks, threads, lds, s);
-}
-
-template hipError_t launch_adj<float>(const AdjArgs<float> &, int, int, int, size_t, hipStream_t);
-template hipError_t launch_adj<double>(const AdjArgs<double> &, int, int, int, size_t, hipStream_t);
 
 // ------------------------------------------------------------------ single-grid adjoint
 //
@@ -874,20 +1266,14 @@ __global__ __launch_bounds__(NT, (NT == 512 ? 4 : 1)) void adj1_kernel(AdjArgs<f
   float *G = sm + L.g_off, *ws = sm + L.ws_off, *st = sm + L.st_off, *db = sm + L.db_off;
   float *tw1 = sm + L.tw_off, *tw2 = tw1 + 2 * g.n1;
   const int per = g.K1 + 1, pitch = L.apitch;
-  const bool persistent = a.work_counter != nullptr;
-  int64_t idx = a.item_base + blockIdx.x;
-  if (!persistent && idx >= a.n_items) return;
   for (int i = threadIdx.x; i < 2 * g.n1; i += NT) tw1[i] = a.tw1[i];
   for (int i = threadIdx.x; i < 2 * g.n2; i += NT) tw2[i] = a.tw2[i];
-  if (!persistent) __syncthreads();
   for (;;) {
-    if (persistent) {
-      if (threadIdx.x == 0) s_item = atomicAdd(a.work_counter, 1);
-      __syncthreads();
-      idx = s_item;
-      __syncthreads();
-      if (idx >= a.n_items) break;
-    }
+    if (threadIdx.x == 0) s_item = atomicAdd(a.work_counter, 1);
+    __syncthreads();
+    const int64_t idx = s_item;
+    __syncthreads();
+    if (idx >= a.n_items) break;
     const AdjItem it = a.items[idx];
     const float *gc = a.fbar + (int64_t)it.cell * g.N1 * g.N2 * 2;
     const float two_lam = a.keep ? float(2.0 * (a.lam ? a.lam[it.cell] : 1.0)) : 1.0f;
@@ -947,9 +1333,8 @@ __global__ __launch_bounds__(NT, (NT == 512 ? 4 : 1)) void adj1_kernel(AdjArgs<f
     const double *wn = a.windows + 3 * (int64_t)it.cell;
     gather1_item<W, NT>(a, G, pitch, it.begin, it.end, float(wn[0]), float(wn[1]), float(wn[2]));
     __syncthreads();
-    if (!persistent) break;
   }
-  if (persistent && threadIdx.x == 0) {
+  if (threadIdx.x == 0) {
     __threadfence();
     const int old = atomicAdd(a.done_counter, 1);
     if (old == (int)gridDim.x - 1) {
@@ -979,15 +1364,13 @@ enufft_status record_stop(enufft_plan_t p, int kind, hipEvent_t start);
 template <typename T>
 void split_scale(int n, T *hi, T *lo);
 
-// Bands per cell: the fewest row bands whose three grids, band spectra and
-// column workspace fit one workgroup's LDS.
-int choose_bands(const Geom &g, int W, size_t elem, size_t lds_max, int *band_rows, size_t *lds) {
-  if (W & 1) return 0;   // uy rows are transformed in pairs: band rows must be even
+// Bands per cell: the fewest row bands whose grid planes fit one workgroup's LDS.
+static int choose_bands(const Geom &g, int W, size_t elem, bool recon, size_t lds_max, int *band_rows, size_t *lds) {
+  if (W & 1) return 0;   // rows are transformed in pairs: band rows must be even
   for (int B = 1; B <= g.n2 / 2; B <<= 1) {
     const int R = g.n2 / B;
-    if (R < 2) break;
-    const AdjLayout L = adj_layout(g, W, R, elem);
-    const size_t bytes = L.total * elem;
+    const size_t bytes = recon && elem == 4 ? rec_layout(g, W, R, elem).total * elem
+                                            : band_layout(g, W, R, elem, recon, ADJ_THREADS).total;
     if (bytes <= lds_max) {
       *band_rows = R;
       *lds = bytes;
@@ -997,14 +1380,17 @@ int choose_bands(const Geom &g, int W, size_t elem, size_t lds_max, int *band_ro
   return 0;
 }
 
-// Adjoint work list: every (cell, band) pair, cells above the chunk target cut
-// into point chunks (gathers need no merge), longest first.
-void build_adj_schedule(enufft_plan_t p, int slots, int B, std::vector<AdjItem> &items) {
-  const int64_t Q = p->n_points;
+// Work list of the cells [c0, c1): every (cell, band) pair, cells above the chunk
+// target cut into point chunks (gathers need no merge), longest first.  A chunk
+// serves at least `least` points of its band: fewer cost less than the band's
+// row transforms.
+static void build_adj_items(enufft_plan_t p, int64_t c0, int64_t c1, int slots, int B, int64_t least,
+                            std::vector<AdjItem> &items) {
+  const int64_t Q = p->offsets[c1] - p->offsets[c0];
   const int64_t per = (int64_t)p->adj_items_per_slot * std::max(1, slots);
-  const int64_t T = std::max<int64_t>(16384, (Q * B + per - 1) / per);
-  items.clear();
-  for (int64_t c = 0; c < p->n_cells; ++c) {
+  const int64_t T = std::max<int64_t>(least * B, (Q * B + per - 1) / per);
+  const size_t first = items.size();
+  for (int64_t c = c0; c < c1; ++c) {
     const int64_t a = p->offsets[c], b = p->offsets[c + 1];
     const int64_t q = b - a;
     if (q == 0) continue;
@@ -1013,37 +1399,18 @@ void build_adj_schedule(enufft_plan_t p, int slots, int B, std::vector<AdjItem> 
       for (int64_t i = 0; i < nch; ++i)
         items.push_back(AdjItem{a + q * i / nch, a + q * (i + 1) / nch, (int32_t)c, band, 0, 0});
   }
-  std::stable_sort(items.begin(), items.end(), [](const AdjItem &x, const AdjItem &y) {
+  std::stable_sort(items.begin() + first, items.end(), [](const AdjItem &x, const AdjItem &y) {
     return (x.end - x.begin) > (y.end - y.begin);
   });
 }
 
-template <typename T>
-hipError_t adj_occ(int W, int threads, bool poly, size_t lds, int *per_cu) {
-  const void *fn = nullptr;
-#define ENUFFT_PICK(WW) \
-  case WW: fn = adj_fn<T, WW>(threads, poly); break;
-  switch (W) {
-    ENUFFT_PICK(4) ENUFFT_PICK(6) ENUFFT_PICK(8) ENUFFT_PICK(10) ENUFFT_PICK(12) ENUFFT_PICK(14) ENUFFT_PICK(16)
-    default: return hipErrorInvalidValue;
-  }
-#undef ENUFFT_PICK
-  hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-  if (e != hipSuccess) return e;
-  return hipOccupancyMaxActiveBlocksPerMultiprocessor(per_cu, fn, threads, lds);
-}
-
-// Release the adjoint schedule so the next call rebuilds it (autotuner).
+// Release the adjoint schedules so the next call rebuilds them (autotuner: while the
+// plan is made, before any reconstruction).
 void adj_reset(enufft_plan_t p) {
-  if (!p->d_adj_items) return;
-  const size_t n = std::max<size_t>(1, p->adj_items.size());
-  dev_release(p, &p->d_adj_items, n * sizeof(AdjItem));
-  dev_release(p, &p->d_rec_part, n * 3 * sizeof(double));
-  dev_release(p, &p->d_cell_items, n * sizeof(int32_t));
-  dev_release(p, &p->d_cell_item_off, (size_t)(p->n_cells + 1) * sizeof(int64_t));
-  dev_release(p, &p->d_cell_off, (size_t)(p->n_cells + 1) * sizeof(int64_t));
-  p->adj_items.clear();
-  dev_release(p, &p->d_adj1_items, std::max<size_t>(1, p->adj1_items.size()) * sizeof(AdjItem));
+  dev_release(p, &p->adj.d_items, std::max<size_t>(16, p->adj.items.size() * sizeof(AdjItem)));
+  dev_release(p, &p->adj.d_cols, std::max<size_t>(16, p->adj.cols_bytes));
+  p->adj = AdjSched{};
+  dev_release(p, &p->d_adj1_items, std::max<size_t>(16, p->adj1_items.size() * sizeof(AdjItem)));
   p->adj1_items.clear();
 }
 
@@ -1060,100 +1427,161 @@ static enufft_status adj_alloc(enufft_plan_t p, void **d, size_t bytes, const ch
   return ENUFFT_OK;
 }
 
-// Lazily set up the adjoint schedule on first use.
-enufft_status adj_prepare(enufft_plan_t p) {
-  if (p->d_adj_items) return ENUFFT_OK;
+static enufft_status adj_upload(enufft_plan_t p, void **d, const void *src, size_t bytes, const char *what) {
+  enufft_status st = adj_alloc(p, d, bytes, what);
+  if (st != ENUFFT_OK || bytes == 0) return st;
+  const hipError_t e = hipMemcpy(*d, src, bytes, hipMemcpyHostToDevice);
+  if (e != hipSuccess) {
+    p->last_error = std::string(what) + " upload: " + hipGetErrorString(e);
+    p->faulted = true;
+    return ENUFFT_EDEVICE;
+  }
+  return ENUFFT_OK;
+}
+
+// Workgroups of `fn` the device holds at once, or 0.
+static int adj_slots(enufft_plan_t p, const void *fn, int threads, size_t lds) {
+  int per_cu = 0;
+  if (!fn || hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess) return 0;
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, threads, lds) != hipSuccess) return 0;
+  return per_cu * p->n_cu;
+}
+
+static const void *band_fn(enufft_plan_t p, bool recon) {
+  if (recon && p->prec == ENUFFT_F32) return rec_fn(p->W, p->es.on != 0);
+  return p->prec == ENUFFT_F64 ? adj_fn_w<double>(p->W, p->es64.on != 0, recon)
+                               : adj_fn_w<float>(p->W, p->es.on != 0, recon);
+}
+
+// The column spectra of one launch take at most this much device memory; larger
+// batches run in groups of cells, one pair of launches each.
+constexpr size_t ADJ_COLS_CAP = (size_t)512 << 20;
+
+// Set up a banded schedule on first use (the gradients' or the reconstruction's).
+static enufft_status band_prepare(enufft_plan_t p, AdjSched *s, bool recon) {
+  if (s->ready) return ENUFFT_OK;
   hipDeviceProp_t prop;
   hipError_t e = hipGetDeviceProperties(&prop, p->device);
   if (e != hipSuccess) {
     p->last_error = std::string("hipGetDeviceProperties: ") + hipGetErrorString(e);
     return ENUFFT_EDEVICE;
   }
-  p->adj_threads = p->prec == ENUFFT_F64 ? 256 : 512;
-  int B = choose_bands(p->geom, p->W, p->elem, (size_t)prop.sharedMemPerBlock, &p->adj_band_rows, &p->adj_lds);
+  AdjSched n;
+  int B = choose_bands(p->geom, p->W, p->elem, recon, (size_t)prop.sharedMemPerBlock, &n.band_rows, &n.lds);
   if (B == 0) {
     p->last_error = "adjoint: fine-grid bands do not fit in LDS";
     return ENUFFT_EUNSUPPORTED;
   }
   // more bands than the minimum (autotuner choice): smaller LDS footprint per item
-  for (int m = p->adj_band_mult; m > 1 && p->geom.n2 / (B * 2) >= 2; m >>= 1) {
+  for (int m = recon ? 1 : p->adj_band_mult; m > 1 && p->geom.n2 / (B * 2) >= 2; m >>= 1) {
     B *= 2;
-    p->adj_band_rows = p->geom.n2 / B;
-    p->adj_lds = adj_layout(p->geom, p->W, p->adj_band_rows, p->elem).total * p->elem;
+    n.band_rows = p->geom.n2 / B;
+    n.lds = band_layout(p->geom, p->W, n.band_rows, p->elem, recon, ADJ_THREADS).total;
   }
-  p->adj_bands = B;
-  int per_cu = 0;
-  e = p->prec == ENUFFT_F64 ? adj_occ<double>(p->W, p->adj_threads, p->es.on != 0, p->adj_lds, &per_cu)
-                            : adj_occ<float>(p->W, p->adj_threads, p->es.on != 0, p->adj_lds, &per_cu);
-  if (e != hipSuccess || per_cu < 1) {
+  n.bands = B;
+  // (the FP32 reconstruction's items transform their own columns)
+  const bool own = recon && p->prec == ENUFFT_F32;
+  const int slots = adj_slots(p, band_fn(p, recon), ADJ_THREADS, n.lds);
+  if (slots < 1) {
     p->last_error = "adjoint kernel cannot be resident";
     return ENUFFT_EDEVICE;
   }
-  const int slots = p->n_cu * per_cu;
-  build_adj_schedule(p, slots, p->adj_bands, p->adj_items);
-  p->adj_blocks = (int)std::min<int64_t>(slots, std::max<int64_t>(1, (int64_t)p->adj_items.size()));
-  const size_t n_items = std::max<size_t>(1, p->adj_items.size());
-  // the items of each cell, ascending (the reconstruction sums a cell's item
-  // partials in this fixed order)
-  std::vector<int64_t> coff(p->n_cells + 1, 0);
-  for (const AdjItem &it : p->adj_items) ++coff[it.cell + 1];
-  for (int64_t c = 0; c < p->n_cells; ++c) coff[c + 1] += coff[c];
-  std::vector<int32_t> citems(n_items, 0);
-  {
-    std::vector<int64_t> pos(coff.begin(), coff.end() - 1);
-    for (size_t i = 0; i < p->adj_items.size(); ++i) citems[pos[p->adj_items[i].cell]++] = (int32_t)i;
+  const size_t per_cell = own ? 0 : (size_t)(recon ? 1 : 2) * p->geom.n2 * (p->geom.K1 + 1) * 2 * p->elem;
+  const int64_t fit = own ? p->n_cells : (int64_t)(ADJ_COLS_CAP / per_cell);
+  const int64_t group = std::max<int64_t>(1, std::min<int64_t>(p->n_cells, fit));
+  for (int64_t c = 0; c < p->n_cells; c += group) {
+    n.cell0.push_back(c);
+    n.first.push_back((int64_t)n.items.size());
+    const int64_t least = p->prec == ENUFFT_F64 ? 512 : own ? 16384 / B : 8192;
+    build_adj_items(p, c, std::min(p->n_cells, c + group), slots, B, least, n.items);
   }
-  void *d = nullptr;
-  enufft_status st = adj_alloc(p, &d, n_items * sizeof(AdjItem), "adjoint item");
-  if (st == ENUFFT_OK) st = adj_alloc(p, &p->d_rec_part, n_items * 3 * sizeof(double), "reconstruction partials");
-  if (st == ENUFFT_OK) st = adj_alloc(p, &p->d_cell_items, n_items * sizeof(int32_t), "cell item list");
-  if (st == ENUFFT_OK)
-    st = adj_alloc(p, &p->d_cell_item_off, (size_t)(p->n_cells + 1) * sizeof(int64_t), "cell item offsets");
-  if (st == ENUFFT_OK) st = adj_alloc(p, &p->d_cell_off, (size_t)(p->n_cells + 1) * sizeof(int64_t), "cell offsets");
+  n.cell0.push_back(p->n_cells);
+  n.first.push_back((int64_t)n.items.size());
+  n.slots = slots;
+  enufft_status st = adj_upload(p, &n.d_items, n.items.data(), n.items.size() * sizeof(AdjItem), "adjoint item");
+  if (st == ENUFFT_OK) {
+    n.cols_bytes = per_cell * (size_t)group;
+    st = adj_alloc(p, &n.d_cols, n.cols_bytes, "adjoint column spectra");
+  }
   if (st != ENUFFT_OK) return st;
-  if (!p->adj_items.empty())
-    e = hipMemcpy(d, p->adj_items.data(), p->adj_items.size() * sizeof(AdjItem), hipMemcpyHostToDevice);
-  if (e == hipSuccess) e = hipMemcpy(p->d_cell_items, citems.data(), n_items * sizeof(int32_t), hipMemcpyHostToDevice);
-  if (e == hipSuccess)
-    e = hipMemcpy(p->d_cell_item_off, coff.data(), coff.size() * sizeof(int64_t), hipMemcpyHostToDevice);
-  if (e == hipSuccess)
-    e = hipMemcpy(p->d_cell_off, p->offsets.data(), p->offsets.size() * sizeof(int64_t), hipMemcpyHostToDevice);
+  n.ready = true;
+  *s = n;
+  return ENUFFT_OK;
+}
+
+// Device copy of the plan's cell offsets (point sort, geometry, reconstruction), made
+// on first use.
+enufft_status cell_offsets(enufft_plan_t p) {
+  if (p->d_cell_off) return ENUFFT_OK;
+  return adj_upload(p, &p->d_cell_off, p->offsets.data(), p->offsets.size() * sizeof(int64_t), "cell offsets");
+}
+
+// Large-cell plans offer the mesh geometry only while a row band of two rows with
+// its cell's column workspace, staged spectrum and band spectra fits one
+// workgroup's LDS (grids up to 256 per axis, about).
+enufft_status geometry_supported(enufft_plan_t p) {
+  if (!p->big) return ENUFFT_OK;
+  hipDeviceProp_t prop;
+  const hipError_t e = hipGetDeviceProperties(&prop, p->device);
   if (e != hipSuccess) {
-    p->last_error = std::string("adjoint item upload: ") + hipGetErrorString(e);
-    p->faulted = true;
+    p->last_error = std::string("hipGetDeviceProperties: ") + hipGetErrorString(e);
     return ENUFFT_EDEVICE;
   }
-  if (p->adj1) {
-    // single-grid adjoint: one item per cell (or chunk of a large cell), no bands;
-    // 512 threads, so two workgroups fit a CU with the compact layout
-    if (const char *ev = std::getenv("ENUFFT_ADJ1_THREADS")) p->adj1_threads = std::atoi(ev) == 1024 ? 1024 : 512;
-    p->adj1_lds = adj1_layout(p->geom, p->adj1_W, sizeof(float), p->adj1_threads).total * sizeof(float);
-    const void *fn = adj1_fn(p->adj1_W, p->adj1_threads);
-    int per1 = 0;
-    e = fn ? hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)p->adj1_lds)
-           : hipErrorInvalidValue;
-    if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per1, fn, p->adj1_threads, p->adj1_lds);
-    if (e != hipSuccess || per1 < 1) {
-      p->last_error = "single-grid adjoint kernel cannot be resident";
-      return ENUFFT_EDEVICE;
-    }
-    const int slots1 = p->n_cu * per1;
-    build_adj_schedule(p, slots1, 1, p->adj1_items);
-    p->adj1_blocks = (int)std::min<int64_t>(slots1, std::max<int64_t>(1, (int64_t)p->adj1_items.size()));
-    void *d1 = nullptr;
-    st = adj_alloc(p, &d1, std::max<size_t>(1, p->adj1_items.size()) * sizeof(AdjItem), "adjoint item");
-    if (st != ENUFFT_OK) return st;
-    if (!p->adj1_items.empty())
-      e = hipMemcpy(d1, p->adj1_items.data(), p->adj1_items.size() * sizeof(AdjItem), hipMemcpyHostToDevice);
-    if (e != hipSuccess) {
-      p->last_error = std::string("adjoint item upload: ") + hipGetErrorString(e);
-      p->faulted = true;
-      return ENUFFT_EDEVICE;
-    }
-    p->d_adj1_items = d1;
+  const Geom &g = p->geom;
+  for (int R = g.n2; R >= 2; R >>= 1) {
+    const size_t rows = (size_t)R + p->W, apitch = (size_t)((g.n1 + p->W) & ~1), per = g.K1 + 1;
+    const size_t cols = (size_t)g.n2 * (2 * per + 2) + adj_stage_elems(g, p->elem);
+    const size_t total = std::max(3 * rows * apitch, cols) + 4 * rows * per + 2 * (size_t)(g.n1 + g.n2);
+    if (total * p->elem <= prop.sharedMemPerBlock) return ENUFFT_OK;
   }
-  p->d_adj_items = d;
-  return ENUFFT_OK;
+  p->last_error = "adjoint: fine-grid bands do not fit in LDS";
+  return ENUFFT_EUNSUPPORTED;
+}
+
+// Lazily set up the adjoint schedule on first use.
+enufft_status adj_prepare(enufft_plan_t p) {
+  if (!p->adj1) return band_prepare(p, &p->adj, false);
+  if (p->d_adj1_items) return ENUFFT_OK;
+  // single-grid adjoint: one item per cell (or chunk of a large cell), no bands;
+  // 512 threads, so two workgroups fit a CU with the compact layout
+  if (const char *ev = std::getenv("ENUFFT_ADJ1_THREADS")) p->adj1_threads = std::atoi(ev) == 1024 ? 1024 : 512;
+  p->adj1_lds = adj1_layout(p->geom, p->adj1_W, sizeof(float), p->adj1_threads).total * sizeof(float);
+  const int slots = adj_slots(p, adj1_fn(p->adj1_W, p->adj1_threads), p->adj1_threads, p->adj1_lds);
+  if (slots < 1) {
+    p->last_error = "single-grid adjoint kernel cannot be resident";
+    return ENUFFT_EDEVICE;
+  }
+  build_adj_items(p, 0, p->n_cells, slots, 1, 16384, p->adj1_items);
+  p->adj1_blocks = (int)std::min<int64_t>(slots, std::max<int64_t>(1, (int64_t)p->adj1_items.size()));
+  void *d = nullptr;
+  enufft_status st =
+      adj_upload(p, &d, p->adj1_items.data(), p->adj1_items.size() * sizeof(AdjItem), "adjoint item");
+  if (st == ENUFFT_OK) p->d_adj1_items = d;
+  return st;
+}
+
+// The reconstruction's schedule, with the items of each cell, ascending (a cell's
+// item partials are summed in this fixed order).
+static enufft_status rec_prepare(enufft_plan_t p) {
+  enufft_status st = band_prepare(p, &p->rec, true);
+  if (st != ENUFFT_OK || p->d_rec_part) return st;
+  const std::vector<AdjItem> &items = p->rec.items;
+  std::vector<int64_t> coff(p->n_cells + 1, 0);
+  for (const AdjItem &it : items) ++coff[it.cell + 1];
+  for (int64_t c = 0; c < p->n_cells; ++c) coff[c + 1] += coff[c];
+  std::vector<int32_t> citems(items.size(), 0);
+  {
+    std::vector<int64_t> pos(coff.begin(), coff.end() - 1);
+    for (size_t i = 0; i < items.size(); ++i) citems[pos[items[i].cell]++] = (int32_t)i;
+  }
+  st = adj_upload(p, &p->d_cell_items, citems.data(), citems.size() * sizeof(int32_t), "cell item list");
+  if (st == ENUFFT_OK)
+    st = adj_upload(p, &p->d_cell_item_off, coff.data(), coff.size() * sizeof(int64_t), "cell item offsets");
+  if (st == ENUFFT_OK) st = cell_offsets(p);
+  if (st == ENUFFT_OK)
+    st = adj_alloc(p, &p->d_rec_part, std::max<size_t>(1, items.size()) * 3 * sizeof(double),
+                   "reconstruction partials");
+  return st;
 }
 
 template <typename T>
@@ -1161,18 +1589,10 @@ AdjArgs<T> make_adj_args(enufft_plan_t p, const void *x, const void *y, const vo
                          const void *fbar, void *gh, void *gx, void *gy) {
   AdjArgs<T> a{};
   a.x = (const T *)x; a.y = (const T *)y; a.h = (const T *)h; a.w = (const T *)w;
-  {
-    const size_t al = 4 * sizeof(T);
-    a.vec4 = ((uintptr_t)x % al == 0 && (uintptr_t)y % al == 0 && (uintptr_t)h % al == 0 &&
-              (uintptr_t)w % al == 0) ? 1 : 0;
-  }
   a.fbar = (const T *)fbar;
   a.keep = nullptr;
   a.lam = nullptr;
   a.grad_h = (T *)gh; a.grad_x = (T *)gx; a.grad_y = (T *)gy;
-  a.items = (const AdjItem *)p->d_adj_items;
-  a.n_items = (int64_t)p->adj_items.size();
-  a.item_base = 0;
   a.work_counter = p->d_counters + 2;
   a.done_counter = p->d_counters + 3;
   a.windows = (const double *)p->d_windows;
@@ -1183,10 +1603,44 @@ AdjArgs<T> make_adj_args(enufft_plan_t p, const void *x, const void *y, const vo
   split_scale<T>(p->n1, &a.s1_hi, &a.s1_lo);
   split_scale<T>(p->n2, &a.s2_hi, &a.s2_lo);
   a.es = p->es;
-  a.bands = p->adj_bands;
-  a.band_rows = p->adj_band_rows;
+  if constexpr (sizeof(T) == 8) a.es64 = p->es64;
+  else a.es64.on = 0;
   a.g = p->geom;
   return a;
+}
+
+// The banded adjoint (rec_part set: the reconstruction): per group of cells, the
+// column transforms, then the band items.
+template <typename T>
+static hipError_t launch_band(enufft_plan_t p, AdjArgs<T> a, const AdjSched &s) {
+  const bool recon = a.rec_part != nullptr;
+  const void *fn = band_fn(p, recon);
+  const int nset = recon ? 1 : 2, ngrp = adj_col_groups(a.g), cg = (a.g.K1 + 1 + ngrp - 1) / ngrp;
+  const size_t lds_cols = ((size_t)a.g.n2 * (2 * cg + 2) + 2 * (size_t)a.g.n2) * sizeof(T);
+  a.bands = s.bands;
+  a.band_rows = s.band_rows;
+  a.cols = (T *)s.d_cols;
+  double *part = a.rec_part;
+  for (size_t q = 0; q + 1 < s.cell0.size(); ++q) {
+    a.items = (const AdjItem *)s.d_items + s.first[q];
+    a.n_items = s.first[q + 1] - s.first[q];
+    if (a.n_items == 0) continue;
+    a.cell0 = (int)s.cell0[q];
+    a.rec_part = recon ? part + 3 * s.first[q] : nullptr;
+    const int64_t nb = (s.cell0[q + 1] - s.cell0[q]) * nset * ngrp;
+    hipError_t e = hipSuccess;
+    if (!(recon && sizeof(T) == 4)) {
+      hipLaunchKernelGGL(adj_cols_kernel<T>, dim3((unsigned)nb), dim3(ADJ_COLS_THREADS), lds_cols, p->stream, a,
+                         nset);
+      e = hipGetLastError();
+      if (e != hipSuccess) return e;
+    }
+    void *args[] = {&a};
+    e = hipLaunchKernel(fn, dim3((unsigned)std::min<int64_t>(s.slots, a.n_items)), dim3(ADJ_THREADS), args, s.lds,
+                        p->stream);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 }  // namespace enufft
@@ -1227,7 +1681,7 @@ enufft_status adjoint_common(enufft_plan_t p, const char *fn, const void *x, con
     auto a = make_adj_args<double>(p, x, y, h, w, fin, grad_h, grad_x, grad_y);
     a.keep = keep;
     a.lam = lam;
-    e = launch_adj<double>(a, p->W, p->adj_blocks, p->adj_threads, p->adj_lds, p->stream);
+    e = launch_band<double>(p, a, p->adj);
   } else if (p->adj1) {
     auto a = make_adj_args<float>(p, x, y, h, w, fin, grad_h, grad_x, grad_y);
     a.keep = keep;
@@ -1239,14 +1693,12 @@ enufft_status adjoint_common(enufft_plan_t p, const char *fn, const void *x, con
     a.es = p->adj1_es;
     a.dsx = (float)(-2.0 * p->n1 / (2.0 * M_PI));   // dt/dx times du/dt of the tap polynomials
     a.dsy = (float)(-2.0 * p->n2 / (2.0 * M_PI));
-    a.bands = 1;
-    a.band_rows = p->n2;
     e = launch_adj1(a, p->adj1_W, p->adj1_blocks, p->adj1_threads, p->adj1_lds, p->stream);
   } else {
     auto a = make_adj_args<float>(p, x, y, h, w, fin, grad_h, grad_x, grad_y);
     a.keep = keep;
     a.lam = lam;
-    e = launch_adj<float>(a, p->W, p->adj_blocks, p->adj_threads, p->adj_lds, p->stream);
+    e = launch_band<float>(p, a, p->adj);
   }
   if (e != hipSuccess) {
     p->last_error = std::string(fn) + " launch: " + hipGetErrorString(e);
@@ -1357,7 +1809,7 @@ extern "C" enufft_status enufft_reconstruct(enufft_plan_t p, const void *x, cons
     p->last_error = "enufft_reconstruct: null point array";
     return ENUFFT_EINVAL;
   }
-  enufft_status st = adj_prepare(p);
+  enufft_status st = rec_prepare(p);
   if (st != ENUFFT_OK) return st;
   hipError_t e = hipSuccess;
   if (p->n_points > 0) {
@@ -1366,13 +1818,13 @@ extern "C" enufft_status enufft_reconstruct(enufft_plan_t p, const void *x, cons
       a.keep = keep;
       a.decon_x = (const double *)p->d_decon_x1;
       a.rec_part = (double *)p->d_rec_part;
-      e = launch_adj<double>(a, p->W, p->adj_blocks, p->adj_threads, p->adj_lds, p->stream);
+      e = launch_band<double>(p, a, p->rec);
     } else {
       auto a = make_adj_args<float>(p, x, y, h, w, coef, h_rec, nullptr, nullptr);
       a.keep = keep;
       a.decon_x = (const float *)p->d_decon_x1;
       a.rec_part = (double *)p->d_rec_part;
-      e = launch_adj<float>(a, p->W, p->adj_blocks, p->adj_threads, p->adj_lds, p->stream);
+      e = launch_band<float>(p, a, p->rec);
     }
   }
   if (e == hipSuccess) {

@@ -78,78 +78,6 @@ __device__ __forceinline__ int big_local(int i0, int t0, int n) {
   return l < BIG_TS + 1 ? l : BIG_TS + 1;
 }
 
-// FP64 per-tap polynomials (EsPoly64): u = 2 v - 1 with v = i0 - t + W/2 clamped
-// to [0, 1]; tap d < W/2 is P_d(u), its mirror W - 1 - d is P_d(-u) (psi is even).
-__device__ __forceinline__ double tap_u64(const FineCoord<double> &c, double halfw) {
-  const double v = ((double(c.i0) - c.hi) - c.lo) + halfw;
-  return 2.0 * fmin(fmax(v, 0.0), 1.0) - 1.0;
-}
-
-// The coefficients of mirror pair d, read where they are used: the offset is
-// opaque to the compiler, so the loads are not hoisted out of the caller's point
-// loop (all W/2 pairs at once would need more scalar registers than there are,
-// and the spills cost a lane move per use).
-__device__ __forceinline__ const double *poly64_pair(const EsPoly64 &cf, int d) {
-  int z = 0;
-  asm volatile("" : "+s"(z));
-  return cf.c + d * (ES64_DEG + 1) + z;
-}
-
-// Mirror pair d at u: P_d(+-u) = E(u^2) +- u O(u^2).
-__device__ __forceinline__ void poly64_pair_eval(const double *cd, double u, double s, double &t0, double &t1) {
-  double e = cd[ES64_DEG - 1], o = cd[ES64_DEG];
-#pragma unroll
-  for (int k = ES64_DEG - 3; k >= 0; k -= 2) {
-    e = fma(e, s, cd[k]);
-    o = fma(o, s, cd[k + 1]);
-  }
-  t0 = fma(u, o, e);
-  t1 = fma(-u, o, e);
-}
-
-// All W taps along both axes, pair by pair (one pair's coefficients live at a time).
-template <int W>
-__device__ __forceinline__ void es_taps_poly64_xy(double ux, double uy, const EsPoly64 &cf, double (&kx)[W],
-                                                  double (&ky)[W]) {
-  static_assert(W % 2 == 0 && ES64_DEG % 2 == 1 && W <= ES64_MAXW, "mirror pairs of an odd-degree fit");
-  const double sx = ux * ux, sy = uy * uy;
-#pragma unroll
-  for (int d = 0; d < W / 2; ++d) {
-    const double *cd = poly64_pair(cf, d);
-    poly64_pair_eval(cd, ux, sx, kx[d], kx[W - 1 - d]);
-    poly64_pair_eval(cd, uy, sy, ky[d], ky[W - 1 - d]);
-  }
-}
-
-// The x taps alone.
-template <int W>
-__device__ __forceinline__ void es_taps_poly64(double u, const EsPoly64 &cf, double (&out)[W]) {
-  static_assert(W % 2 == 0 && ES64_DEG % 2 == 1 && W <= ES64_MAXW, "mirror pairs of an odd-degree fit");
-  const double s = u * u;
-#pragma unroll
-  for (int d = 0; d < W / 2; ++d) poly64_pair_eval(poly64_pair(cf, d), u, s, out[d], out[W - 1 - d]);
-}
-
-// One tap, dd in [0, W): Horner on its pair's coefficients at +-u (dd uniform
-// across the wave, so the coefficient loads stay scalar).
-template <int W>
-__device__ __forceinline__ double es_tap_poly64(double u, const EsPoly64 &cf, int dd) {
-  const bool m = dd >= W / 2;
-  const double *cd = cf.c + (m ? W - 1 - dd : dd) * (ES64_DEG + 1);
-  const double x = m ? -u : u;
-  double acc = cd[ES64_DEG];
-#pragma unroll
-  for (int k = ES64_DEG - 1; k >= 0; --k) acc = fma(acc, x, cd[k]);
-  return acc;
-}
-
-// Kernel-argument form of EsPoly64 per precision (FP32 kernels carry only the flag).
-struct NoPoly64 {
-  int on;
-};
-template <typename T>
-using Poly64Of = typename std::conditional<sizeof(T) == 8, EsPoly64, NoPoly64>::type;
-
 // The W kernel values of one point along one axis: the plan's per-tap
 // polynomials (FP32, W <= ES_MAXW) when POLY; for FP64 plans their FP64 ones
 // when the plan carries them; else psi itself.

@@ -6,6 +6,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 namespace enufft {
 
 // ------------------------------------------------------------------ records
@@ -35,17 +37,26 @@ struct EsPoly {
   float c[(ES_MAXW / 2) * (ES_DEG + 1)];   // taps 0 .. W/2 - 1, tap-major, ascending powers of u = 2 v - 1
 };
 
-// The same per-tap form in FP64 for the large-cell kernels of FP64 plans: degree
-// 13 reproduces the taps of the widths those plans use (W = 10 .. 16, eps 1e-9 ..
-// 1e-14) to about 5e-13 at W = 12 (the outer tap's square-root branch point at the
-// edge of the support limits the fit, not the degree).  Also by value in the
-// kernel arguments: its loads are scalar, the same address for every lane.
+// The same per-tap form in FP64 for FP64 plans: degree 13 reproduces the taps to
+// about 5e-13 at W = 12 and 6e-15 at W = 14 (the outer tap's square-root branch
+// point at the edge of the support limits the fit up to W = 12, not the degree).
+// The table is in device memory, read through scalar loads (the same address for
+// every lane): by value in the kernel arguments, a pair chosen in a loop made the
+// compiler copy the whole argument block to every lane's scratch.
 constexpr int ES64_DEG = 13;
 constexpr int ES64_MAXW = 16;
 struct EsPoly64 {
   int on;
-  double c[(ES64_MAXW / 2) * (ES64_DEG + 1)];   // as EsPoly
+  const double *c;   // (W / 2)(ES64_DEG + 1) coefficients, as EsPoly
 };
+typedef const double __attribute__((address_space(4))) *ScalarTable;
+
+// Kernel-argument form of EsPoly64 per precision (FP32 kernels carry only the flag).
+struct NoPoly64 {
+  int on;
+};
+template <typename T>
+using Poly64Of = typename std::conditional<sizeof(T) == 8, EsPoly64, NoPoly64>::type;
 
 // Fine-grid and mode-box geometry.
 struct Geom {
@@ -77,6 +88,7 @@ struct FwdArgs {
   int vec4;                  // x, y, h, w are 16-byte aligned: load runs of 4 points
   int acc;                   // bytes per LDS grid cell: 8 (FP64 sums) or 4 (FP32 sums)
   EsPoly es;                 // FP32 plans: per-tap kernel polynomials (es.on = 0: exact kernel)
+  Poly64Of<T> es64;          // FP64 plans: the same in FP64
   Geom g;
 };
 
@@ -89,7 +101,6 @@ struct AdjArgs {
   T *grad_h, *grad_x, *grad_y;
   const AdjItem *items;
   int64_t n_items;
-  int64_t item_base;
   int *work_counter;
   int *done_counter;
   const double *windows;
@@ -99,9 +110,11 @@ struct AdjArgs {
   T beta;
   T s1_hi, s1_lo, s2_hi, s2_lo;
   EsPoly es;                   // as in FwdArgs (the single-grid adjoint: its own kernel's taps)
+  Poly64Of<T> es64;
   T dsx, dsy;                  // single-grid adjoint: -2 n1 / (2 pi), -2 n2 / (2 pi)
-  int vec4;                    // x, y, h, w are 16-byte aligned: load runs of 4 points
   int bands, band_rows;        // row bands per cell and rows per band
+  T *cols;                     // banded adjoint: column spectra of cells cell0 .. (see adj_cols_kernel)
+  int cell0;
   double *rec_part;            // reconstruction mode: per item (sum (t - h_rec)^2, sum t^2, sum w t^2)
   Geom g;
 };
@@ -293,6 +306,71 @@ __device__ __forceinline__ void es_taps(const FineCoord<T> &c, T beta, const EsP
   const T zsc = T(2) / T(W);
 #pragma unroll
   for (int d = 0; d < W; ++d) out[d] = ker_eval(c.offset(d) * zsc, beta);
+}
+
+// FP64 per-tap polynomials (EsPoly64): u = 2 v - 1 with v = i0 - t + W/2 clamped
+// to [0, 1]; tap d < W/2 is P_d(u), its mirror W - 1 - d is P_d(-u) (psi is even).
+__device__ __forceinline__ double tap_u64(const FineCoord<double> &c, double halfw) {
+  const double v = ((double(c.i0) - c.hi) - c.lo) + halfw;
+  return 2.0 * fmin(fmax(v, 0.0), 1.0) - 1.0;
+}
+
+// The coefficients of mirror pair d, read where they are used: the offset is
+// opaque to the compiler, so the loads are not hoisted out of the caller's point
+// loop (all W/2 pairs at once would need more scalar registers than there are,
+// and the spills cost a lane move per use).
+__device__ __forceinline__ ScalarTable poly64_pair(const EsPoly64 &cf, int d) {
+  int z = 0;
+  asm volatile("" : "+s"(z));
+  return (ScalarTable)cf.c + d * (ES64_DEG + 1) + z;
+}
+
+// Mirror pair d at u: P_d(+-u) = E(u^2) +- u O(u^2).
+__device__ __forceinline__ void poly64_pair_eval(ScalarTable cd, double u, double s, double &t0, double &t1) {
+  double e = cd[ES64_DEG - 1], o = cd[ES64_DEG];
+#pragma unroll
+  for (int k = ES64_DEG - 3; k >= 0; k -= 2) {
+    e = fma(e, s, cd[k]);
+    o = fma(o, s, cd[k + 1]);
+  }
+  t0 = fma(u, o, e);
+  t1 = fma(-u, o, e);
+}
+
+// All W taps along both axes, pair by pair (one pair's coefficients live at a time).
+template <int W>
+__device__ __forceinline__ void es_taps_poly64_xy(double ux, double uy, const EsPoly64 &cf, double (&kx)[W],
+                                                  double (&ky)[W]) {
+  static_assert(W % 2 == 0 && ES64_DEG % 2 == 1 && W <= ES64_MAXW, "mirror pairs of an odd-degree fit");
+  const double sx = ux * ux, sy = uy * uy;
+#pragma unroll
+  for (int d = 0; d < W / 2; ++d) {
+    const ScalarTable cd = poly64_pair(cf, d);
+    poly64_pair_eval(cd, ux, sx, kx[d], kx[W - 1 - d]);
+    poly64_pair_eval(cd, uy, sy, ky[d], ky[W - 1 - d]);
+  }
+}
+
+// The x taps alone.
+template <int W>
+__device__ __forceinline__ void es_taps_poly64(double u, const EsPoly64 &cf, double (&out)[W]) {
+  static_assert(W % 2 == 0 && ES64_DEG % 2 == 1 && W <= ES64_MAXW, "mirror pairs of an odd-degree fit");
+  const double s = u * u;
+#pragma unroll
+  for (int d = 0; d < W / 2; ++d) poly64_pair_eval(poly64_pair(cf, d), u, s, out[d], out[W - 1 - d]);
+}
+
+// One tap, dd in [0, W): Horner on its pair's coefficients at +-u (dd uniform
+// across the wave, so the coefficient loads stay scalar).
+template <int W>
+__device__ __forceinline__ double es_tap_poly64(double u, const EsPoly64 &cf, int dd) {
+  const bool m = dd >= W / 2;
+  const ScalarTable cd = (ScalarTable)cf.c + (m ? W - 1 - dd : dd) * (ES64_DEG + 1);
+  const double x = m ? -u : u;
+  double acc = cd[ES64_DEG];
+#pragma unroll
+  for (int k = ES64_DEG - 1; k >= 0; --k) acc = fma(acc, x, cd[k]);
+  return acc;
 }
 
 // ------------------------------------------------------------------ small DFTs

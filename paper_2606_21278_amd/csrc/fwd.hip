@@ -51,6 +51,29 @@ __device__ __forceinline__ void spread_point(const FwdArgs<T> &a, A *grid, T c, 
                                              const FineCoord<T> &fy) {
   const Geom &g = a.g;
   const int pitch = grid_pitch<P>(g);
+  if constexpr (P != 0 && sizeof(T) == 8) {
+    // FP64: the x taps, then the rows in mirror pairs, whose y taps come from one
+    // polynomial pair (its coefficients read where they are used)
+    T kx[W];
+    es_taps_poly64<W>(tap_u64(fx, double(W) * 0.5), a.es64, kx);
+    const T u = tap_u64(fy, double(W) * 0.5), s = u * u;
+    const int c0 = fx.i0, r0 = fy.i0 & (g.n2 - 1);
+#pragma unroll
+    for (int d = 0; d < W / 2; ++d) {
+      T ta, tb;
+      poly64_pair_eval(poly64_pair(a.es64, d), u, s, ta, tb);
+      ta *= c;
+      tb *= c;
+      A *pa = grid + (r0 + d) * pitch, *pb = grid + (r0 + W - 1 - d) * pitch;
+#pragma unroll
+      for (int dx = 0; dx < W; ++dx) {
+        const int col = (c0 + dx) & (g.n1 - 1);
+        __hip_atomic_fetch_add(pa + col, ta * kx[dx], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        __hip_atomic_fetch_add(pb + col, tb * kx[dx], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      }
+    }
+    return;
+  }
   T tx[W], ty[W];
   taps<T, W, P>(a, fx, tx);
   taps<T, W, P>(a, fy, ty);
@@ -635,7 +658,8 @@ __global__ __launch_bounds__(NT, (fwd_min_waves<A, NT>())) void fwd_kernel(FwdAr
 // The compiled variants: FP32 with the kernel polynomial (W <= 8) also has
 // polynomial builds, one with the constant pitch of the 128-wide grid and one
 // for any pitch, used when the plan carries the polynomial; those builds come
-// with an FP64 and an FP32 LDS grid (acc = 8 or 4 bytes per cell).
+// with an FP64 and an FP32 LDS grid (acc = 8 or 4 bytes per cell).  FP64 has a
+// polynomial build for any pitch.
 template <typename T, int W>
 constexpr bool has_pitch128() {
   return sizeof(T) == 4 && W <= ES_MAXW;
@@ -659,6 +683,8 @@ static const void *fwd_fn(int threads, int pitch, int acc) {
                       : fwd_fn_threads<T, double, W, FWD_POLY_ANY>(threads);
   }
   if (acc != 8) return nullptr;
+  if constexpr (sizeof(T) == 8)
+    if (pitch == FWD_POLY_ANY) return fwd_fn_threads<T, double, W, FWD_POLY_ANY>(threads);
   return fwd_fn_threads<T, double, W, 0>(threads);
 }
 
@@ -679,7 +705,7 @@ static const void *fwd_fn_w(int W, int threads, int pitch, int acc) {
 template <typename T>
 hipError_t launch_fwd(const FwdArgs<T> &a, int W, int blocks, int threads, size_t lds, hipStream_t s) {
   if (threads != 256 && threads != 512 && threads != 1024) return hipErrorInvalidValue;
-  const void *fn = fwd_fn_w<T>(W, threads, fwd_variant_pitch(a.g, a.es), a.acc);
+  const void *fn = fwd_fn_w<T>(W, threads, fwd_variant_pitch(a.g, a.es, a.es64.on), a.acc);
   if (!fn) return hipErrorInvalidValue;
   void *args[] = {const_cast<FwdArgs<T> *>(&a)};
   return hipLaunchKernel(fn, dim3(blocks), dim3(threads), args, lds, s);

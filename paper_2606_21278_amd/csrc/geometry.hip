@@ -423,7 +423,8 @@ hipError_t geo_occupancy(size_t lds, int *per_cu) {
 
 }  // namespace
 
-enufft_status adj_prepare(enufft_plan_t p);
+enufft_status cell_offsets(enufft_plan_t p);
+enufft_status geometry_supported(enufft_plan_t p);
 
 }  // namespace enufft
 
@@ -446,8 +447,8 @@ extern "C" enufft_status enufft_cell_geometry(enufft_plan_t p, const double *tri
   if (!tri) return geo_fail(p, ENUFFT_EINVAL, "null triangle array");
   if (p->n_points > 0 && (!x || !y || !h || !xb || !yb || !hb || !wb))
     return geo_fail(p, ENUFFT_EINVAL, "null point or output array");
-  // device copy of the cell offsets (shared with the adjoint's schedule)
-  st = adj_prepare(p);
+  st = geometry_supported(p);
+  if (st == ENUFFT_OK) st = cell_offsets(p);
   if (st != ENUFFT_OK) return st;
   const bool vor = o.weights == ENUFFT_WEIGHTS_VORONOI;
   GeoParams g{o.frame, o.mask, o.weights, o.raster, o.deplane ? 1 : 0, o.eta, o.floor_frac};

@@ -13,11 +13,6 @@ hipError_t launch_fwd(const FwdArgs<T> &a, int W, int blocks, int threads, size_
 template <typename T>
 hipError_t fwd_occupancy(int W, int threads, int pitch, int acc, size_t lds, int *blocks_per_cu);
 
-template <typename T>
-hipError_t launch_adj(const AdjArgs<T> &a, int W, int blocks, int threads, size_t lds, hipStream_t s);
-template <typename T>
-hipError_t adj_occupancy(int W, int threads, size_t lds, int *blocks_per_cu);
-
 // Per-wave queue of deferred point groups in the forward kernel (entries).
 constexpr int FWD_QCAP = 128;
 // Row pitch of the 128-wide fine grid (64-mode boxes at sigma 2), for which
@@ -29,7 +24,8 @@ constexpr int FWD_PITCH128 = 130;
 // the pitch read at run time, 0 for the general one (exact kernel or
 // polynomial, chosen at run time).
 constexpr int FWD_POLY_ANY = -1;
-inline int fwd_variant_pitch(const Geom &g, const EsPoly &es) {
+inline int fwd_variant_pitch(const Geom &g, const EsPoly &es, int es64_on) {
+  if (es64_on) return FWD_POLY_ANY;
   if (!es.on) return 0;
   return g.pitch == FWD_PITCH128 ? FWD_PITCH128 : FWD_POLY_ANY;
 }

@@ -222,15 +222,17 @@ double fit_tap_poly(int W, int deg, const F &f, std::vector<double> &coef) {
   coef.assign((size_t)W * (deg + 1), 0.0);
   double maxerr = 0.0;
   const int n = deg + 1;
+  std::vector<double> cheb(n), yn(n), un(n), ct((size_t)n * n);
+  for (int j = 0; j < n; ++j)
+    for (int i = 0; i < n; ++i) ct[(size_t)j * n + i] = std::cos(j * M_PI * (i + 0.5) / n);
   for (int d = 0; d < W; ++d) {
-    std::vector<double> cheb(n, 0.0), yn(n), un(n);
     for (int i = 0; i < n; ++i) {
       un[i] = std::cos(M_PI * (i + 0.5) / n);
       yn[i] = f(d, ((0.5 * (un[i] + 1.0)) + d - 0.5 * W) * 2.0 / W);
     }
     for (int j = 0; j < n; ++j) {
       double s = 0.0;
-      for (int i = 0; i < n; ++i) s += yn[i] * std::cos(j * M_PI * (i + 0.5) / n);
+      for (int i = 0; i < n; ++i) s += yn[i] * ct[(size_t)j * n + i];
       cheb[j] = (j == 0 ? 1.0 : 2.0) * s / n;
     }
     // Chebyshev -> monomial: T_0 = 1, T_1 = u, T_{j+1} = 2 u T_j - T_{j-1}
@@ -245,8 +247,9 @@ double fit_tap_poly(int W, int deg, const F &f, std::vector<double> &coef) {
       }
     for (int j = 0; j < n; ++j)
       for (int k = 0; k < n; ++k) coef[(size_t)d * n + k] += cheb[j] * Tm[j][k];
-    for (int i = 0; i <= 2000; ++i) {
-      const double v = i / 2000.0, u = 2.0 * v - 1.0;
+    // (the kernel is even: taps W / 2 .. W - 1 mirror the first half)
+    for (int i = 0; i <= 400 && d < (W + 1) / 2; ++i) {
+      const double v = i / 400.0, u = 2.0 * v - 1.0;
       double acc = coef[(size_t)d * n + deg];
       for (int k = deg - 1; k >= 0; --k) acc = acc * u + coef[(size_t)d * n + k];
       maxerr = std::max(maxerr, std::fabs(acc - f(d, (v + d - 0.5 * W) * 2.0 / W)));
@@ -403,7 +406,7 @@ void build_fwd_schedule(enufft_plan_t p, int slots) {
 enufft_status set_fwd_threads(enufft_plan_t p, int threads, size_t lds_limit) {
   if (threads != 256 && threads != 512 && threads != 1024)
     return fail(p, ENUFFT_EINVAL, "forward threads must be 256, 512 or 1024");
-  const int vp = fwd_variant_pitch(p->geom, p->es);
+  const int vp = fwd_variant_pitch(p->geom, p->es, p->es64.on);
   // FP32 sums in LDS exist only for the FP32 polynomial builds
   if (p->prec == ENUFFT_F64 || vp == 0) p->fwd_acc = 8;
   const size_t lds = fwd_lds_bytes(p->geom, p->W, threads, (size_t)p->fwd_acc);
@@ -587,9 +590,10 @@ enufft_status enufft_plan(enufft_plan_t *out, int64_t n_cells, const int64_t *ce
     }
   }
 
-  // FP64 large-cell plans: the same per-tap form in FP64 (even widths), kept when its fit
-  // is at least ten times below the requested accuracy
-  if (p->prec == ENUFFT_F64 && big && W % 2 == 0 && W <= enufft::ES64_MAXW) {
+  // FP64 plans: the same per-tap form in FP64 (even widths), kept when its fit is at
+  // least ten times below the requested accuracy
+  std::vector<double> es64;
+  if (p->prec == ENUFFT_F64 && W % 2 == 0 && W <= enufft::ES64_MAXW) {
     const char *ev = std::getenv("ENUFFT_POLY64");
     if (!(ev && std::atoi(ev) == 0)) {
       std::vector<double> cf;
@@ -597,7 +601,7 @@ enufft_status enufft_plan(enufft_plan_t *out, int64_t n_cells, const int64_t *ce
       if (err <= 0.1 * opts->eps) {
         p->es_poly_err = err;
         p->es64.on = 1;
-        for (size_t i = 0; i < (size_t)(W / 2) * (enufft::ES64_DEG + 1); ++i) p->es64.c[i] = cf[i];
+        es64.assign(cf.begin(), cf.begin() + (size_t)(W / 2) * (enufft::ES64_DEG + 1));
       }
     }
   }
@@ -690,6 +694,12 @@ enufft_status enufft_plan(enufft_plan_t *out, int64_t n_cells, const int64_t *ce
     }
     return e2 == hipSuccess ? ENUFFT_OK : hip_fail(p, e2, what);
   };
+  if (p->es64.on) {
+    void *d = nullptr;
+    st = upload_table(&d, es64, "tables");
+    if (st != ENUFFT_OK) { std::string m = p->last_error; free_plan(p); return fail(nullptr, st, m); }
+    p->es64.c = (const double *)d;
+  }
   for (auto &tb : {std::make_pair(&p->d_decon_x, &dx), std::make_pair(&p->d_decon_y, &dy),
                    std::make_pair(&p->d_decon_x1, &dx1),
                    std::make_pair(&p->d_tw1, &tw1), std::make_pair(&p->d_tw2, &tw2)}) {
@@ -752,10 +762,11 @@ enufft_status enufft_get_info(enufft_plan_t p, enufft_plan_info *info) {
   info->n_points = p->n_points;
   info->n_items_fwd = (int64_t)p->fwd_items.size();
   info->n_split_cells = p->n_split;
-  info->n_items_adj = (int64_t)p->adj_items.size();
-  info->adj_bands = p->adj_bands;
+  info->n_items_adj = (int64_t)(p->adj1 ? p->adj1_items.size() : p->adj.items.size());
+  info->adj_bands = p->adj.bands;
   info->fwd_threads = p->fwd_threads; info->fwd_blocks = p->fwd_blocks;
-  info->adj_threads = p->adj_threads; info->adj_blocks = p->adj_blocks;
+  info->adj_threads = p->adj1 ? p->adj1_threads : 512;
+  info->adj_blocks = p->adj1 ? p->adj1_blocks : (int)std::min<int64_t>(p->adj.slots, info->n_items_adj);
   info->workspace_bytes = p->workspace_bytes;
   info->kernel_poly_err = p->es_poly_err;
   info->tuned = p->tuned;
@@ -855,6 +866,8 @@ FwdArgs<T> make_fwd_args(enufft_plan_t p, const void *x, const void *y, const vo
   split_scale<T>(p->n2, &a.s2_hi, &a.s2_lo);
   a.acc = p->fwd_acc;
   a.es = p->es;
+  if constexpr (sizeof(T) == 8) a.es64 = p->es64;
+  else a.es64.on = 0;
   a.g = p->geom;
   return a;
 }

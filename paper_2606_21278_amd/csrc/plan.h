@@ -24,6 +24,17 @@ struct UnitTable {                 // EMS units for one (use_pairs, exclude_dc) 
   int4 *d_mode_unit = nullptr;     // [M]: (rep, partner, unit id, 0) of each mode's unit, rep -1: none
 };
 
+// A banded schedule (the gradients' or the reconstruction's): row bands per cell and
+// the work items, in groups of cells whose column spectra are held at once.
+struct AdjSched {
+  bool ready = false;
+  int bands = 1, band_rows = 0, slots = 0;
+  size_t lds = 0, cols_bytes = 0;
+  std::vector<AdjItem> items;
+  std::vector<int64_t> cell0, first;   // per group: its first cell and item (+ sentinels)
+  void *d_items = nullptr, *d_cols = nullptr;
+};
+
 }  // namespace enufft
 
 struct enufft_plan_s {
@@ -72,28 +83,25 @@ struct enufft_plan_s {
   int adj1_threads = 512, adj1_blocks = 0;
   size_t adj1_lds = 0;
 
-  // adjoint schedule (also used by the reconstruction diagnostics)
-  std::vector<enufft::AdjItem> adj_items;
+  // banded schedules of the adjoint and of the reconstruction
+  enufft::AdjSched adj, rec;
   void *d_rec_part = nullptr;        // [items][3] doubles: per-item reconstruction sums
   void *d_cell_items = nullptr;      // int32 item indices grouped by cell (ascending)
   void *d_cell_item_off = nullptr;   // int64 [n_cells + 1] offsets into d_cell_items
   void *d_cell_off = nullptr;        // int64 [n_cells + 1] the plan's cell offsets
   int32_t *d_sort_perm = nullptr;    // [n_points] enufft_sort_points' permutation when the caller asks for none
   void *d_sort_rec = nullptr;        // [n_points] enufft_sort_points' interleaved (x, y, h, w) records
-  int adj_bands = 1, adj_band_rows = 0;
-  int adj_threads = 512, adj_blocks = 0;
-  size_t adj_lds = 0;
 
   // device memory
   void *d_windows = nullptr;
-  void *d_fwd_items = nullptr, *d_fwd_items_cell = nullptr, *d_adj_items = nullptr;
+  void *d_fwd_items = nullptr, *d_fwd_items_cell = nullptr;
   int *d_counters = nullptr;       // [0] fwd work, [1] fwd done, [2] adj work, [3] adj done
   int *d_cell_counters = nullptr;
   void *d_partial = nullptr;
   void *d_decon_x = nullptr, *d_decon_y = nullptr, *d_tw1 = nullptr, *d_tw2 = nullptr;
   void *d_decon_x1 = nullptr;      // 1 / p_x(|k|) without the plan's scale (reconstruction)
   enufft::EsPoly es{};             // FP32 plans: kernel polynomial coefficients (es.on = 0: exact)
-  enufft::EsPoly64 es64{};         // FP64 large-cell plans: the same in FP64 (es64.on = 0: exact)
+  enufft::EsPoly64 es64{};         // FP64 plans: the same in FP64 (es64.on = 0: exact)
   double es_poly_err = 0.0;        // max |poly - psi| over the fit interval
   enufft::UnitTable units[2][2];
   int64_t workspace_bytes = 0;

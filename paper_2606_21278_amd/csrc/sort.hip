@@ -166,7 +166,7 @@ hipError_t launch_sort(enufft_plan_t p, const void *x, const void *y, const void
 
 }  // namespace
 
-enufft_status adj_prepare(enufft_plan_t p);
+enufft_status cell_offsets(enufft_plan_t p);
 
 }  // namespace enufft
 
@@ -187,7 +187,7 @@ extern "C" enufft_status enufft_sort_points(enufft_plan_t p, const void *x, cons
   // large cells: the order their tiled spreading uses (by 32 x 32 tile); calls on
   // input in that order skip the per-call scatter
   if (p->big) return big_sort_points(p, x, y, h, w, xs, ys, hs, ws, perm);
-  st = adj_prepare(p);   // device copy of the cell offsets
+  st = cell_offsets(p);
   if (st != ENUFFT_OK) return st;
   // plan-owned workspace, allocated on first use and kept for later calls (freed by
   // enufft_destroy): the interleaved records, and the permutation when the caller
