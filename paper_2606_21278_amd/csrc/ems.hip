@@ -30,11 +30,11 @@ struct EmsArgs {
   int32_t *k_star;
   double *stats;
   const int2 *units;          // (rep, partner | -1), ascending unit id
-  const int4 *mode_unit;      // [M]: (rep, partner | -1, unit id, 0) of each mode's unit; rep -1: no unit
   int J;
   int M;                      // modes per cell = N1 * N2
   int N1, N2;                 // mode box (row-major, N1 modes per row)
   int64_t cell_begin, cell_end;
+  int dc;                     // index of the excluded k = 0 mode, or -1
   int k_min, k_max;
   double alpha_min, alpha_max, delta, w1, w2;
 };
@@ -156,16 +156,9 @@ __device__ __forceinline__ void wave_sort_desc(double (&e)[R], int lane) {
 
 // Energy of unit u (FP64; products of FP32 values are exact in FP64) from its
 // loaded coefficients and mode weights (1 without weights: the product by 1
-// is exact).  The same arithmetic serves the sort (unit order), the tie
-// ranking and the keep pass (mode order), so a unit's energy is bit-identical
-// in all three.  Loads are unconditional (a missing partner reads the
-// representative and is masked).
-//
-// Every product and sum is rounded on its own (contraction into fused
-// multiply-adds is off here): the keep pass forms a pair's energy from either
-// member first, and only separately rounded member terms make
-// w_a |f_a|^2 + w_b |f_b|^2 the same bits in both orders when the weights are
-// not 1.
+// is exact).  Loads are unconditional (a missing partner reads the
+// representative and is masked).  Every product and sum is rounded on its own
+// (contraction into fused multiply-adds is off here), as the large cells' passes do.
 __device__ __forceinline__ double member_energy(double re, double im, double w) {
 #pragma clang fp contract(off)
   return (re * re + im * im) * w;
@@ -205,28 +198,20 @@ __device__ __forceinline__ double flow_weight(const FlowRec &fl, int kx, int ky)
   return fabs(act);
 }
 
-// Weight of mode m (row-major, N1 per row): the flow weight, the caller's
-// mode_weight, or 1.
-__device__ __forceinline__ double mode_w(const EmsArgs &a, const FlowRec &fl, int m) {
-  if (fl.on) {
-    const int r = m / a.N1, i = m - r * a.N1;
-    return flow_weight(fl, i - (a.N1 >> 1), r - (a.N2 >> 1));
-  }
-  return a.mode_weight ? a.mode_weight[m] : 1.0;
+// Row of mode m (row-major, N1 per row; the float quotient is within one of the
+// true one for the at most 2^13 modes of these kernels).
+__device__ __forceinline__ int mode_row(int m, int N1, float inv_n1) {
+  int r = (int)((float)m * inv_n1);
+  r -= r * N1 > m;
+  r += (r + 1) * N1 <= m;
+  return r;
 }
 
-template <typename C>
-__device__ __forceinline__ double pair_energy(const EmsArgs &a, const FlowRec &fl, const C *f, int rep, int partner) {
-  const int pq = partner >= 0 ? partner : rep;
-  const bool wt = a.mode_weight || fl.on;
-  const double wr = wt ? mode_w(a, fl, rep) : 1.0, wp = wt ? mode_w(a, fl, pq) : 1.0;
-  return pair_energy_v<C>(f[rep], f[pq], wr, wp, partner >= 0);
-}
-
-// The energies of n units (or of the units of n modes) with all loads of the
-// batch issued before any is used: member indices first, then coefficients,
-// then (with mode weights) the weights.  reps[i] < 0 marks an entry with no
-// unit (its energy is returned as 0).
+// The energies of n units with all loads of the batch issued before any is used:
+// member indices first, then coefficients, then (with mode weights) the weights.
+// reps[i] < 0 marks an entry with no unit (its energy is returned as 0).  The flow
+// weight is the same for k and -k, bit for bit (the wave vector enters squared, or in
+// one product whose magnitude is taken), so a pair's is evaluated once.
 template <typename C, int N>
 __device__ __forceinline__ void batch_energy(const EmsArgs &a, const FlowRec &fl, const C *f, const int (&reps)[N],
                                              const int (&partners)[N], double (&e)[N]) {
@@ -237,25 +222,30 @@ __device__ __forceinline__ void batch_energy(const EmsArgs &a, const FlowRec &fl
     fr[i] = f[rep];
     fp[i] = f[partners[i] >= 0 ? partners[i] : rep];
   }
-  if (a.mode_weight || fl.on) {
-    double wr[N], wp[N];
+  double wr[N], wp[N];
+#pragma unroll
+  for (int i = 0; i < N; ++i) wr[i] = wp[i] = 1.0;
+  if (fl.on) {
+    const float inv_n1 = 1.0f / (float)a.N1;
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      const int m = reps[i] >= 0 ? reps[i] : 0, r = mode_row(m, a.N1, inv_n1);
+      wr[i] = wp[i] = flow_weight(fl, m - r * a.N1 - (a.N1 >> 1), r - (a.N2 >> 1));
+    }
+  } else if (a.mode_weight) {
 #pragma unroll
     for (int i = 0; i < N; ++i) {
       const int rep = reps[i] >= 0 ? reps[i] : 0;
-      wr[i] = mode_w(a, fl, rep);
-      wp[i] = mode_w(a, fl, partners[i] >= 0 ? partners[i] : rep);
+      wr[i] = a.mode_weight[rep];
+      wp[i] = a.mode_weight[partners[i] >= 0 ? partners[i] : rep];
     }
-#pragma unroll
-    for (int i = 0; i < N; ++i)
-      e[i] = reps[i] >= 0 ? pair_energy_v<C>(fr[i], fp[i], wr[i], wp[i], partners[i] >= 0) : 0.0;
-  } else {
-#pragma unroll
-    for (int i = 0; i < N; ++i)
-      e[i] = reps[i] >= 0 ? pair_energy_v<C>(fr[i], fp[i], 1.0, 1.0, partners[i] >= 0) : 0.0;
   }
+#pragma unroll
+  for (int i = 0; i < N; ++i)
+    e[i] = reps[i] >= 0 ? pair_energy_v<C>(fr[i], fp[i], wr[i], wp[i], partners[i] >= 0) : 0.0;
 }
 
-// Workgroup-wide sum / integer sum / integer min / exclusive scan for NW
+// Workgroup-wide sum / integer min / exclusive scan for NW
 // waves (NW = 1: the wave operations alone, no barrier).  Every thread gets
 // the result; the summation order is fixed.
 template <int NW>
@@ -268,21 +258,6 @@ __device__ __forceinline__ double block_sum(double v, double *red, int wave) {
     if ((threadIdx.x & 63) == 0) red[wave] = v;
     __syncthreads();
     double s = 0.0;
-#pragma unroll
-    for (int w = 0; w < NW; ++w) s += red[w];
-    return s;
-  }
-}
-template <int NW>
-__device__ __forceinline__ int block_sum_i(int v, int *red, int wave) {
-  v = wave_sum_i(v);
-  if constexpr (NW == 1) {
-    return v;
-  } else {
-    __syncthreads();
-    if ((threadIdx.x & 63) == 0) red[wave] = v;
-    __syncthreads();
-    int s = 0;
 #pragma unroll
     for (int w = 0; w < NW; ++w) s += red[w];
     return s;
@@ -321,33 +296,68 @@ __device__ __forceinline__ V block_exclusive_scan(V v, V *red, int wave, int lan
   }
 }
 
-// five waves per SIMD (96 VGPRs) for up to three waves per cell; the four-wave
-// form's sort does not fit that and keeps four; the wide forms (below) need one
-// workgroup per CU
+// Waves per SIMD asked of the compiler: four for up to four waves per cell (the
+// unit energies stay in registers beside the sort's); the wide forms (below) need
+// one workgroup per CU.
 template <int NW>
 constexpr int ems_min_waves() {
-  return NW <= 3 ? 5 : NW == 4 ? 4 : (NW + 3) / 4;
+  return NW <= 4 ? 4 : (NW + 3) / 4;
 }
 
-// One workgroup of NW waves per cell; thread t holds sort positions
-// t R .. t R + R - 1.  Each wave sorts its 64 R energies in registers, the
-// sorted runs are merged pairwise through LDS (merge path: every thread finds
-// where its R outputs start by binary search and merges them sequentially),
-// and the scores are read from the sorted array.
+// Sorted values in LDS: position j at j + j / 16, so that threads reading 16 (or 4)
+// consecutive positions each fall on different banks.
+__host__ __device__ __forceinline__ constexpr int ems_sidx(int j) { return j + (j >> 4); }
+
+// Buckets of the value sort, two 16-bit counters per word: about 3,072, or two per
+// sorted position for the small forms.  They take the unused tail of the sorted
+// array where it is long enough, else LDS of their own.
+template <int R, int NW>
+constexpr int ems_bucket_words() {
+  constexpr int w = (1536 + 64 * NW - 1) / (64 * NW);
+  return 64 * NW * (w < R ? w : R);
+}
+template <int R, int NW>
+__host__ __device__ __forceinline__ int ems_bucket_at(int J) {   // first word of the buckets
+  constexpr int top = 2 * ems_sidx(64 * R * NW);
+  const int own = 2 * ems_sidx(J + 1) + 2;
+  return own + ems_bucket_words<R, NW>() <= top ? own : top;
+}
+template <int R, int NW>
+__host__ __device__ __forceinline__ size_t ems_lds_bytes(int J) {
+  const int top = 2 * ems_sidx(64 * R * NW), end = ems_bucket_at<R, NW>(J) + ems_bucket_words<R, NW>();
+  return 4 * (size_t)(end > top ? end : top);
+}
+
+// A bucket with more values than this goes to the comparison network instead.
+constexpr int EMS_BUCKET_MAX = 64;
+
+// One workgroup of NW waves per cell.  Thread t holds the energies of units
+// t, t + NT, ... in registers from the first load to the keep flags, so the
+// coefficients are read once (a second read of the kept few gives the retained
+// power).  The order of eq. (sorted_energy) is by energy, ties by ascending unit
+// id.  Every quantity before the cut depends only on the sorted energy values, so
+// the sort carries values only; which of several units tied at the cut energy are
+// kept is settled afterwards by ascending id (a prefix count of the ties).
 //
-// The order of eq. (sorted_energy) is by energy, ties by ascending unit id.
-// Every quantity before the cut depends only on the sorted energy values, so
-// the sort carries values only; which of several units tied at the cut energy
-// are kept is settled afterwards by ascending id (a prefix count of the ties).
+// The sort: non-negative FP64 values order as their bits, so the top 32 bits, scaled
+// over the range present, give a bucket; one LDS counter per bucket, its scan, and a
+// rank inside the bucket (a handful of values) place every value.  Zeros (modes
+// outside a flow's propagating band) are the tail and take no bucket.  A crowded
+// bucket (more than EMS_BUCKET_MAX values, for instance a flat spectrum's ties) or a
+// negative weighted energy sends the cell to the comparison network instead: each wave sorts its 64 R values
+// in registers and the runs are merged pairwise through LDS (merge path).
+//
+// What bounds it: latency and LDS work per cell (20,480 cells of 2,111 units: 0.76 GB of
+// coefficients and masks).  With the network for every cell, each thread's units
+// consecutive (64 cache lines per load) and the coefficients and a unit record per
+// mode read again for the keep flags the launch took 0.88 ms; now 0.56 ms (and
+// eight flow steps of 2,560 cells 1.31 to 0.53 ms).
 template <typename T, int R, int NW>
 __global__ __launch_bounds__(64 * NW, (ems_min_waves<NW>())) void ems_kernel(EmsArgs a) {
   constexpr int NT = 64 * NW, JW = 64 * R, JP = JW * NW;
-  __shared__ double sorted[JP];
-  // the tie flags reuse the sorted values' storage: they are written only after
-  // every read of the sorted values (see the tie ranking below)
-  uint8_t *tie_kept = reinterpret_cast<uint8_t *>(sorted);
-  __shared__ double redd[NW];
-  __shared__ int redi[NW];
+  extern __shared__ __align__(16) double sorted[];   // position j at ems_sidx(j)
+  __shared__ double red0[NW], red1[NW];
+  __shared__ int redi0[NW], redi1[NW];
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, t = threadIdx.x;
   // cell: the output index; in flow mode step s of cell c is v = s n_cells_f + c
   // and reads the coefficients of cell c
@@ -363,13 +373,10 @@ __global__ __launch_bounds__(64 * NW, (ems_min_waves<NW>())) void ems_kernel(Ems
   }
   const int J = a.J;
 
-  // eq. (energy) / (weighted_e), unit u = position t R + r.  Padding is +0,
-  // which sorts among real zero energies; positions >= J are excluded from
-  // every sum below, and equal values are interchangeable.
+  // eq. (energy) / (weighted_e): e[r] is unit r NT + t (0 beyond J).  Batches of EB
+  // units: few memory latencies per thread, few live registers.
   double e[R];
   double t1 = 0.0, t2 = 0.0;
-  // batches of EB units: few memory latencies per thread, few live registers
-  // (the kernel's register peak sets how many workgroups share a CU)
   constexpr int EB = R < 4 ? R : 4;
   static_assert(R % EB == 0, "energy batches must divide R");
 #pragma unroll
@@ -377,7 +384,7 @@ __global__ __launch_bounds__(64 * NW, (ems_min_waves<NW>())) void ems_kernel(Ems
     int reps[EB], partners[EB];
 #pragma unroll
     for (int i = 0; i < EB; ++i) {
-      const int u = t * R + r0 + i;
+      const int u = (r0 + i) * NT + t;
       const int2 un = a.units[u < J ? u : max(J - 1, 0)];
       reps[i] = u < J ? un.x : -1;
       partners[i] = un.y;
@@ -387,57 +394,155 @@ __global__ __launch_bounds__(64 * NW, (ems_min_waves<NW>())) void ems_kernel(Ems
 #pragma unroll
     for (int i = 0; i < EB; ++i) e[r0 + i] = eb[i];
   }
+  // sums, and the range of the top words of the non-zero energies (a negative or
+  // unordered one makes the minimum -1)
+  int kmin = INT_MAX, nkmax = 0;
 #pragma unroll
   for (int r = 0; r < R; ++r) {
     t1 += e[r];
     t2 += e[r] * e[r];
+    const int hi = __double2hiint(e[r]);
+    if (e[r] != 0.0) {
+      kmin = min(kmin, e[r] > 0.0 ? hi : -1);
+      nkmax = min(nkmax, -hi);
+    }
   }
-  const double T1 = block_sum<NW>(t1, redd, wave);
-  const double T2 = block_sum<NW>(t2, redd, wave);
+  constexpr int BW = ems_bucket_words<R, NW>(), NB = 2 * BW, WPT = BW / NT;
+  unsigned *bkt = reinterpret_cast<unsigned *>(sorted) + ems_bucket_at<R, NW>(J);
+#pragma unroll
+  for (int i = 0; i < WPT; ++i) bkt[i * NT + t] = 0u;
+  double T1 = wave_sum(t1), T2 = wave_sum(t2);
+  kmin = wave_min_i(kmin);
+  nkmax = wave_min_i(nkmax);
+  if (lane == 0) {
+    red0[wave] = T1; red1[wave] = T2; redi0[wave] = kmin; redi1[wave] = nkmax;
+  }
+  __syncthreads();
+  if constexpr (NW > 1) {
+    T1 = T2 = 0.0;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+      T1 += red0[w];
+      T2 += red1[w];
+      kmin = min(kmin, redi0[w]);
+      nkmax = min(nkmax, redi1[w]);
+    }
+  }
 
-  // eq. (sorted_energy): runs of JW per wave, then merges
-  wave_sort_desc<R>(e, lane);
+  // eq. (sorted_energy).  The bucket falls with the energy; a float product of the
+  // (exactly converted or rounded, either way monotone) distance from the largest
+  // keeps the order.
+  int pos[R];   // bucket | place in the bucket << 16, or -1
+  int crowd = 0;
+  if (kmin >= 0) {
+    const float scale = (float)NB / ((float)(-nkmax - kmin) + 1.0f) * 0.999999f;
 #pragma unroll
-  for (int r = 0; r < R; ++r) sorted[t * R + r] = e[r];
-#pragma unroll
-  for (int width = JW; width < JP; width *= 2) {
+    for (int r = 0; r < R; ++r) {
+      pos[r] = -1;
+      if (e[r] != 0.0) {
+        const int b = min(NB - 1, (int)((float)(-nkmax - __double2hiint(e[r])) * scale));
+        const int sh = (b & 1) * 16;
+        pos[r] = b | (int)((atomicAdd(&bkt[b >> 1], 1u << sh) >> sh) & 0xffffu) << 16;
+      }
+    }
     __syncthreads();
-    const int o0 = t * R;                       // first output position
-    const int base = o0 / (2 * width) * (2 * width);
-    // runs A = [base, base + width) and B = the rest of the pair (shorter, or
-    // empty, at the end when NW is not a power of two)
-    const int lb = min(width, max(0, JP - base - width));
-    const double *A = sorted + base, *B = A + width;
-    const int d = o0 - base;                    // outputs before mine in this merged run
-    double out[R];
-    if (lb > 0) {
-      int lo = d > lb ? d - lb : 0, hi = d < width ? d : width;
-      while (lo < hi) {                         // first d outputs take lo from A
-        const int mid = (lo + hi) >> 1;
-        if (A[mid] >= B[d - 1 - mid]) lo = mid + 1;
-        else hi = mid;
-      }
-      int ia = lo, ib = d - lo;
+    unsigned wv[WPT];
+    int sum = 0;
 #pragma unroll
-      for (int r = 0; r < R; ++r) {
-        const double va = A[min(ia, width - 1)], vb = B[min(ib, lb - 1)];   // in bounds; guarded below
-        const bool take_a = ib >= lb || (ia < width && va >= vb);
-        out[r] = take_a ? va : vb;
-        ia += take_a;
-        ib += !take_a;
-      }
-    } else {                                    // unpaired run: already in place
+    for (int i = 0; i < WPT; ++i) {
+      wv[i] = bkt[t * WPT + i];
+      const int lo = wv[i] & 0xffff, hi = wv[i] >> 16;
+      sum += lo + hi;
+      crowd = max(crowd, max(lo, hi));
+    }
+    int run = block_exclusive_scan<NW, int>(sum, redi0, wave, lane);
 #pragma unroll
-      for (int r = 0; r < R; ++r) out[r] = sorted[o0 + r];
+    for (int i = 0; i < WPT; ++i) {   // counts become starts
+      const int lo = wv[i] & 0xffff, hi = wv[i] >> 16;
+      bkt[t * WPT + i] = (unsigned)run | (unsigned)(run + lo) << 16;
+      run += lo + hi;
+    }
+    crowd = -block_min_i<NW>(-crowd, redi1, wave);
+    if (t == NT - 1) redi0[0] = run;   // non-zero values
+    __syncthreads();
+  }
+  if (kmin >= 0 && crowd <= EMS_BUCKET_MAX) {
+    const int nnz = redi0[0];
+    auto start = [&](int b) -> int { return b < NB ? (int)((bkt[b >> 1] >> ((b & 1) * 16)) & 0xffffu) : nnz; };
+    // values in bucket order first, without the padding (position j at j)
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+      if (pos[r] >= 0) sorted[start(pos[r] & 0xffff) + (pos[r] >> 16)] = e[r];
+    __syncthreads();
+    // rank inside the bucket: values above, and equal ones at earlier places (a value
+    // there need only exceed the next FP64 below e)
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      if (pos[r] < 0) continue;
+      const int b = pos[r] & 0xffff, s0 = start(b), s1 = start(b + 1), mine = s0 + (pos[r] >> 16);
+      int rank = s0;
+      if (s1 - s0 > 1) {
+        const double below = __longlong_as_double(__double_as_longlong(e[r]) - 1);
+        for (int q = s0; q < s1; q += 2) {
+          const double v0 = sorted[q], v1 = sorted[q + 1];   // (q + 1 <= J: inside the array)
+          rank += v0 > (q < mine ? below : e[r]);
+          rank += q + 1 < s1 && v1 > (q + 1 < mine ? below : e[r]);
+        }
+      }
+      pos[r] = rank;
     }
     __syncthreads();
 #pragma unroll
-    for (int r = 0; r < R; ++r) sorted[o0 + r] = out[r];
-  }
-  __syncthreads();
+    for (int r = 0; r < R; ++r)
+      if (pos[r] >= 0) sorted[ems_sidx(pos[r])] = e[r];
+    for (int j = nnz + t; j < J; j += NT) sorted[ems_sidx(j)] = 0.0;
+    __syncthreads();
+  } else {
+    // the comparison network: runs of JW per wave, then merges
+    __syncthreads();
+    double v[R];
 #pragma unroll
-  for (int r = 0; r < R; ++r) e[r] = sorted[t * R + r];   // this thread's sorted positions
-  const double enext = (t * R + R < JP) ? sorted[t * R + R] : 0.0;
+    for (int r = 0; r < R; ++r) v[r] = e[r];
+    wave_sort_desc<R>(v, lane);
+#pragma unroll
+    for (int r = 0; r < R; ++r) sorted[ems_sidx(t * R + r)] = v[r];
+#pragma unroll 1
+    for (int width = JW; width < JP; width *= 2) {
+      __syncthreads();
+      const int o0 = t * R;                       // first output position
+      const int base = o0 / (2 * width) * (2 * width);
+      // runs A = [base, base + width) and B = the rest of the pair (shorter, or
+      // empty, at the end when NW is not a power of two)
+      const int lb = min(width, max(0, JP - base - width));
+      const int d = o0 - base;                    // outputs before mine in this merged run
+      auto A = [&](int i) { return sorted[ems_sidx(base + i)]; };
+      auto B = [&](int i) { return sorted[ems_sidx(base + width + i)]; };
+      if (lb > 0) {
+        int lo = d > lb ? d - lb : 0, hi = d < width ? d : width;
+        while (lo < hi) {                         // first d outputs take lo from A
+          const int mid = (lo + hi) >> 1;
+          if (A(mid) >= B(d - 1 - mid)) lo = mid + 1;
+          else hi = mid;
+        }
+        int ia = lo, ib = d - lo;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+          const double va = A(min(ia, width - 1)), vb = B(min(ib, lb - 1));   // in bounds; guarded below
+          const bool take_a = ib >= lb || (ia < width && va >= vb);
+          v[r] = take_a ? va : vb;
+          ia += take_a;
+          ib += !take_a;
+        }
+      } else {                                    // unpaired run: already in place
+#pragma unroll
+        for (int r = 0; r < R; ++r) v[r] = sorted[ems_sidx(o0 + r)];
+      }
+      __syncthreads();
+#pragma unroll
+      for (int r = 0; r < R; ++r) sorted[ems_sidx(o0 + r)] = v[r];
+    }
+    __syncthreads();
+  }
 
   const int Jmax = J < a.k_max ? J : a.k_max;
   // eq. (n_eff) over all J units, clipped by the budget
@@ -445,40 +550,41 @@ __global__ __launch_bounds__(64 * NW, (ems_min_waves<NW>())) void ems_kernel(Ems
   const double nclip = neff < (double)Jmax ? neff : (double)Jmax;
   // eq. (s_delta) over the first J_max - 1 gaps
   double sd = 0.0;
-#pragma unroll
-  for (int r = 0; r < R; ++r) {
-    const int j = t * R + r;
-    if (j < Jmax - 1) {
-      const double ea = e[r], eb = (r + 1 < R) ? e[r + 1 < R ? r + 1 : r] : enext;
-      double term;
-      if (eb == 0.0 && ea == 0.0) term = 1.0;
-      else if (eb == 0.0) term = 0.0;
-      else term = exp(-(ea / eb - 1.0) / a.delta);
-      sd += term;
-    }
+  for (int j = t; j < Jmax - 1; j += NT) {
+    const double ea = sorted[ems_sidx(j)], eb = sorted[ems_sidx(j + 1)];
+    double term;
+    if (eb == 0.0 && ea == 0.0) term = 1.0;
+    else if (eb == 0.0) term = 0.0;
+    else term = exp(-(ea / eb - 1.0) / a.delta);
+    sd += term;
   }
-  const double sdsum = block_sum<NW>(sd, redd, wave);
+  // eq. (f_cum): running sum in sorted order, thread t at positions t R .. t R + R - 1
+  double loc = 0.0;
+#pragma unroll
+  for (int r = 0; r < R; ++r)
+    if (t * R + r < J) loc += sorted[ems_sidx(t * R + r)];
+  const double sdsum = block_sum<NW>(sd, red0, wave);
   const double sdel = Jmax < 2 ? 1.0 : sdsum / (double)(Jmax - 1);
   // eqs. (c_score), (alpha_c)
   const double Cs = (Jmax > 0 ? a.w1 * nclip / (double)Jmax : 0.0) + a.w2 * sdel;
   const double alphaC = a.alpha_min + (a.alpha_max - a.alpha_min) * Cs;
-
-  // eq. (f_cum): running sum in sorted order; the first K with theta(K) >= alpha_C
-  double loc = 0.0;
-#pragma unroll
-  for (int r = 0; r < R; ++r)
-    if (t * R + r < J) loc += e[r];
-  double run = block_exclusive_scan<NW, double>(loc, redd, wave, lane);
+  // the first K with theta(K) >= alpha_C
+  const double run0 = block_exclusive_scan<NW, double>(loc, red1, wave, lane);
   int kc = INT_MAX;
+  // (a division only near the crossing: below `under` the quotient is short of alpha_C;
+  // non-negative energies cross once, in the one thread whose sums straddle it)
+  const double under = alphaC * T1 * (1.0 - 1e-12), over = alphaC * T1 * (1.0 + 1e-12);
+  if (T1 > 0.0 && t * R < J && (kmin < 0 || (run0 + loc >= under && run0 <= over))) {
+    double v[R], run = run0;
 #pragma unroll
-  for (int r = 0; r < R; ++r) {
-    const int j = t * R + r;
-    if (j < J) {
-      run += e[r];
-      if (T1 > 0.0 && kc == INT_MAX && run / T1 >= alphaC) kc = j + 1;
+    for (int r = 0; r < R; ++r) v[r] = sorted[ems_sidx(t * R + r)];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      run += v[r];
+      if (kc == INT_MAX && t * R + r < J && !(run < under) && run / T1 >= alphaC) kc = t * R + r + 1;
     }
   }
-  kc = block_min_i<NW>(kc, redi, wave);
+  kc = block_min_i<NW>(kc, redi0, wave);
   // eq. (k_elastic)
   int kstar;
   if (!(T1 > 0.0)) {
@@ -490,108 +596,86 @@ __global__ __launch_bounds__(64 * NW, (ems_min_waves<NW>())) void ems_kernel(Ems
   }
   // cut energy E_(K*), the retained sum of the first K* sorted energies, and
   // how many units lie strictly above the cut or at it
-  const double eth = kstar > 0 ? sorted[kstar - 1] : 0.0;
+  const double eth = kstar > 0 ? sorted[ems_sidx(kstar - 1)] : 0.0;
   double part = 0.0;
-  int cgt = 0, ceq = 0;
+  int cgt = 0;
 #pragma unroll
   for (int r = 0; r < R; ++r) {
-    const int j = t * R + r;
-    if (j < kstar) part += e[r];
-    if (j < J) {
-      cgt += e[r] > eth;
-      ceq += e[r] == eth;
-    }
+    const int j = t * R + r, u = r * NT + t;
+    if (j < kstar) part += sorted[ems_sidx(j)];
+    if (u < J) cgt += (e[r] > eth) + ((e[r] == eth) << 16);   // at most 4,096 of each
   }
-  const double th = block_sum<NW>(part, redd, wave);
-  const int ngt = block_sum_i<NW>(cgt, redi, wave);
-  const int neq = block_sum_i<NW>(ceq, redi, wave);
-  const int need = kstar - ngt;   // units kept at the cut energy, lowest ids first
+  double th = wave_sum(part);
+  int cnt = wave_sum_i(cgt);
+  if constexpr (NW > 1) {
+    __syncthreads();
+    if (lane == 0) { red0[wave] = th; redi1[wave] = cnt; }
+    __syncthreads();
+    th = 0.0;
+    cnt = 0;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) { th += red0[w]; cnt += redi1[w]; }
+  }
+  const int need = kstar - (cnt & 0xffff);   // units kept at the cut energy, lowest ids first
+  const int neq = cnt >> 16;
 
   // Ties straddling the cut (more units at the cut energy than kept there):
   // rank the tied units by id.  Otherwise every unit at the cut is kept.
-  const bool split_ties = kstar > 0 && neq > need;
-  if (split_ties) {   // the same in every thread
-    __syncthreads();   // every thread has read the sorted values (tie_kept overwrites them)
-    int ties = 0;
+  unsigned kept = 0;   // bit r: unit r NT + t is kept
+  if (kstar > 0 && neq > need) {   // the same in every thread
+    int before = 0;
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-      const int u = t * R + r;
-      const int2 un = a.units[u < J ? u : max(J - 1, 0)];
-      ties += (u < J && pair_energy<C>(a, fl, f, un.x, un.y) == eth);
-    }
-    int rank = block_exclusive_scan<NW, int>(ties, redi, wave, lane);
+      const bool tie = r * NT + t < J && e[r] == eth;
+      const uint64_t m = __ballot(tie);
+      int rank = before + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+      int total = __popcll(m);
+      if constexpr (NW > 1) {
+        __syncthreads();
+        if (lane == 0) redi0[wave] = total;
+        __syncthreads();
+        total = 0;
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const int u = t * R + r;
-      const int2 un = a.units[u < J ? u : max(J - 1, 0)];
-      const bool tie = u < J && pair_energy<C>(a, fl, f, un.x, un.y) == eth;
-      tie_kept[u] = tie && rank < need;
-      rank += tie;
+        for (int w = 0; w < NW; ++w) {
+          if (w < wave) rank += redi0[w];
+          total += redi0[w];
+        }
+      }
+      before += total;
+      if (r * NT + t < J && (e[r] > eth || (tie && rank < need))) kept |= 1u << r;
     }
-    __syncthreads();
+  } else if (kstar > 0) {
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+      if (r * NT + t < J && e[r] >= eth) kept |= 1u << r;
   }
 
-  // modes (coalesced): keep flags and the retained power.  Batches of UK modes
-  // per thread: all loads of a batch come before its stores (the byte stores
-  // may alias the coefficients as far as the compiler knows, so a store
-  // between loads would serialise them).  A paired mode's other member is its
-  // mirror -k, whose index follows from the mode's own, so the coefficient
-  // loads need not wait for the mode's unit record and a batch costs about
-  // one memory latency.  The energy e(m) + e(mirror) equals the unit's
-  // e(rep) + e(partner) bit for bit (the same member terms; FP64 addition
-  // commutes).
+  // keep flags and the retained power: consecutive lanes take consecutive units, whose
+  // representatives ascend and partners descend by one, so the byte stores coalesce
   double pw = 0.0;
   uint8_t *kout = a.keep ? a.keep + cell * a.M : nullptr;   // flow mode may skip the masks
-  constexpr int UK = 2;
-  const int N1 = a.N1, hm1 = 2 * (a.N1 >> 1), hm2 = 2 * (a.N2 >> 1);
-  const float inv_n1 = 1.0f / (float)N1;
-  for (int m0 = t; m0 < a.M; m0 += UK * NT) {
-    uint8_t v[UK];
-    int4 mu[UK];
-    C fm[UK], fo[UK];
-    int mm[UK], mo[UK];
 #pragma unroll
-    for (int u = 0; u < UK; ++u) {
-      const int m = min(m0 + u * NT, a.M - 1);
-      // row and column of m (the float quotient is within one of the true one)
-      int r = (int)((float)m * inv_n1);
-      r -= r * N1 > m;
-      r += (r + 1) * N1 <= m;
-      const int ri = hm2 - r, ii = hm1 - (m - r * N1);   // the mirror's row and column
-      mm[u] = m;
-      mo[u] = (ri < a.N2 && ii < N1) ? ri * N1 + ii : m;
-      mu[u] = a.mode_unit[m];
-      fm[u] = f[m];
-      fo[u] = f[mo[u]];
+  for (int r = 0; r < R; ++r) {
+    const int u = r * NT + t;
+    if (u >= J) continue;
+    const bool k = (kept >> r) & 1u;
+    if (!kout && !k) continue;
+    const int2 un = a.units[u];
+    if (kout) {
+      kout[un.x] = k;
+      if (un.y >= 0) kout[un.y] = k;
     }
-    double eu[UK];
-    if (a.mode_weight || fl.on) {
-      double wm[UK], wo[UK];
-#pragma unroll
-      for (int u = 0; u < UK; ++u) {
-        wm[u] = mode_w(a, fl, mm[u]);
-        wo[u] = mode_w(a, fl, mo[u]);
+    if (k) {
+      const C fa = f[un.x];
+      pw += (double)fa.x * (double)fa.x + (double)fa.y * (double)fa.y;
+      if (un.y >= 0) {
+        const C fb = f[un.y];
+        pw += (double)fb.x * (double)fb.x + (double)fb.y * (double)fb.y;
       }
-#pragma unroll
-      for (int u = 0; u < UK; ++u) eu[u] = pair_energy_v<C>(fm[u], fo[u], wm[u], wo[u], mu[u].y >= 0);
-    } else {
-#pragma unroll
-      for (int u = 0; u < UK; ++u) eu[u] = pair_energy_v<C>(fm[u], fo[u], 1.0, 1.0, mu[u].y >= 0);
-    }
-#pragma unroll
-    for (int u = 0; u < UK; ++u) {
-      const bool keep = m0 + u * NT < a.M && mu[u].x >= 0 && kstar > 0 &&
-                        (eu[u] > eth || (eu[u] == eth && (!split_ties || tie_kept[mu[u].z])));
-      v[u] = keep;
-      if (keep) pw += (double)fm[u].x * (double)fm[u].x + (double)fm[u].y * (double)fm[u].y;
-    }
-#pragma unroll
-    for (int u = 0; u < UK; ++u) {
-      const int m = m0 + u * NT;
-      if (m < a.M && kout) kout[m] = v[u];
     }
   }
-  const double P = block_sum<NW>(pw, redd, wave);
+  if (kout && t == 0 && a.dc >= 0) kout[a.dc] = 0;   // the excluded mode belongs to no unit
+  const double P = block_sum<NW>(pw, red1, wave);
   if (t == 0) {
     a.k_star[cell] = kstar;
     double *st = a.stats + cell * 8;
@@ -692,32 +776,35 @@ bool ems_wide(const enufft_plan_t p, int J, int64_t blocks) {
   return waves < (int64_t)p->n_cu * 8;
 }
 
+template <typename T, int R, int NW>
+static hipError_t launch_ems_form(const EmsArgs &a, int J, int blocks, hipStream_t s) {
+  hipLaunchKernelGGL((ems_kernel<T, R, NW>), dim3(blocks), dim3(64 * NW), (ems_lds_bytes<R, NW>(J)), s, a);
+  return hipGetLastError();
+}
+
 template <typename T>
 hipError_t launch_ems_t(const EmsArgs &a, int J, int blocks, hipStream_t s, bool wide) {
-  const dim3 g(blocks);
   if (wide && J > 256) {
     // few cells: each cell's latency is the launch's, so more waves per cell, four
-    // values per lane (a shorter register sort, more merge rounds through LDS)
-    if (J <= 512) hipLaunchKernelGGL((ems_kernel<T, 4, 2>), g, dim3(128), 0, s, a);
-    else if (J <= 768) hipLaunchKernelGGL((ems_kernel<T, 4, 3>), g, dim3(192), 0, s, a);
-    else if (J <= 1024) hipLaunchKernelGGL((ems_kernel<T, 4, 4>), g, dim3(256), 0, s, a);
-    else if (J <= 1536) hipLaunchKernelGGL((ems_kernel<T, 4, 6>), g, dim3(384), 0, s, a);
-    else if (J <= 2048) hipLaunchKernelGGL((ems_kernel<T, 4, 8>), g, dim3(512), 0, s, a);
-    else if (J <= 3072) hipLaunchKernelGGL((ems_kernel<T, 4, 12>), g, dim3(768), 0, s, a);
-    else if (J <= 4096) hipLaunchKernelGGL((ems_kernel<T, 4, 16>), g, dim3(1024), 0, s, a);
-    else return hipErrorInvalidValue;
-    return hipGetLastError();
+    // values per lane
+    if (J <= 512) return launch_ems_form<T, 4, 2>(a, J, blocks, s);
+    if (J <= 768) return launch_ems_form<T, 4, 3>(a, J, blocks, s);
+    if (J <= 1024) return launch_ems_form<T, 4, 4>(a, J, blocks, s);
+    if (J <= 1536) return launch_ems_form<T, 4, 6>(a, J, blocks, s);
+    if (J <= 2048) return launch_ems_form<T, 4, 8>(a, J, blocks, s);
+    if (J <= 3072) return launch_ems_form<T, 4, 12>(a, J, blocks, s);
+    if (J <= 4096) return launch_ems_form<T, 4, 16>(a, J, blocks, s);
+    return hipErrorInvalidValue;
   }
-  if (J <= 64) hipLaunchKernelGGL((ems_kernel<T, 1, 1>), g, dim3(64), 0, s, a);
-  else if (J <= 128) hipLaunchKernelGGL((ems_kernel<T, 2, 1>), g, dim3(64), 0, s, a);
-  else if (J <= 256) hipLaunchKernelGGL((ems_kernel<T, 4, 1>), g, dim3(64), 0, s, a);
-  else if (J <= 512) hipLaunchKernelGGL((ems_kernel<T, 8, 1>), g, dim3(64), 0, s, a);
-  else if (J <= 1024) hipLaunchKernelGGL((ems_kernel<T, 16, 1>), g, dim3(64), 0, s, a);
-  else if (J <= 2048) hipLaunchKernelGGL((ems_kernel<T, 16, 2>), g, dim3(128), 0, s, a);
-  else if (J <= 3072) hipLaunchKernelGGL((ems_kernel<T, 16, 3>), g, dim3(192), 0, s, a);
-  else if (J <= 4096) hipLaunchKernelGGL((ems_kernel<T, 16, 4>), g, dim3(256), 0, s, a);
-  else return hipErrorInvalidValue;
-  return hipGetLastError();
+  if (J <= 64) return launch_ems_form<T, 1, 1>(a, J, blocks, s);
+  if (J <= 128) return launch_ems_form<T, 2, 1>(a, J, blocks, s);
+  if (J <= 256) return launch_ems_form<T, 4, 1>(a, J, blocks, s);
+  if (J <= 512) return launch_ems_form<T, 8, 1>(a, J, blocks, s);
+  if (J <= 1024) return launch_ems_form<T, 16, 1>(a, J, blocks, s);
+  if (J <= 2048) return launch_ems_form<T, 16, 2>(a, J, blocks, s);
+  if (J <= 3072) return launch_ems_form<T, 16, 3>(a, J, blocks, s);
+  if (J <= 4096) return launch_ems_form<T, 16, 4>(a, J, blocks, s);
+  return hipErrorInvalidValue;
 }
 
 enufft_status record_start(enufft_plan_t p, int kind, hipEvent_t *ev);
@@ -732,7 +819,9 @@ enufft_status ems_launch(enufft_plan_t p, const void *f, const enufft_ems_params
     return big_ems(p, f, prm, mode_weight, keep, k_star, stats, ut, cell_begin, cell_count);
   EmsArgs a{};
   a.f = f; a.mode_weight = mode_weight; a.keep = keep; a.k_star = k_star; a.stats = stats;
-  a.units = ut->d_units; a.mode_unit = ut->d_mode_unit; a.J = ut->J; a.M = p->N1 * p->N2;
+  a.units = ut->d_units; a.J = ut->J;
+  a.dc = prm->exclude_dc ? (p->N2 / 2) * p->N1 + p->N1 / 2 : -1;
+  a.M = p->N1 * p->N2;
   a.N1 = p->N1; a.N2 = p->N2;
   a.cell_begin = cell_begin;
   a.cell_end = cell_begin + cell_count;
@@ -802,7 +891,9 @@ extern "C" enufft_status enufft_ems_flow(enufft_plan_t p, const void *f, const e
   enufft::EmsArgs a{};
   a.f = f; a.mode_weight = nullptr; a.flow = flow; a.n_cells_f = p->n_cells;
   a.keep = keep; a.k_star = k_star; a.stats = stats;
-  a.units = ut->d_units; a.mode_unit = ut->d_mode_unit; a.J = ut->J; a.M = p->N1 * p->N2;
+  a.units = ut->d_units; a.J = ut->J;
+  a.dc = prm->exclude_dc ? (p->N2 / 2) * p->N1 + p->N1 / 2 : -1;
+  a.M = p->N1 * p->N2;
   a.N1 = p->N1; a.N2 = p->N2;
   a.cell_begin = 0;
   a.cell_end = (int64_t)n_steps * p->n_cells;
