@@ -1369,6 +1369,8 @@ __global__ __launch_bounds__(256) void big_gather_kernel(BigTileArgs<T> a) {
   });
 }
 
+#include "big_mfma.h"
+
 // Gradients back to input order: one read of the sorted-order record per point
 // (at its sorted position) and coalesced writes of the three outputs.  Input
 // already in tile order needs none: the gather wrote the gradients itself.
@@ -1796,7 +1798,11 @@ enufft_status type1_t(enufft_plan_t p, const T *x, const T *y, const T *h, const
         a.partial = p->big_partial;
         a.work_counter = p->big_work;
         a.done_counter = p->big_work + 1;
-        e = by_width<T, SpreadW>(p->W, a, tile_blocks(p, n), p->stream);
+        bool done = false;
+        if constexpr (sizeof(T) == 8) {
+          if ((done = m64_use(p->W, a.es64))) e = m64_launch(p->W, a, false, tile_blocks(p, n), p->stream);
+        }
+        if (!done) e = by_width<T, SpreadW>(p->W, a, tile_blocks(p, n), p->stream);
         // cells whose points are in fine-cell order: the run kernel (the kernel
         // above returned at once for them; the flag is known on the device only)
         if constexpr (sizeof(T) == 4) {
@@ -1859,7 +1865,11 @@ enufft_status adjoint_t(enufft_plan_t p, const T *x, const T *y, const T *h, con
       a.gy = gy ? gy + a0 : nullptr;
       a.work_counter = p->big_work + 2;
       a.done_counter = p->big_work + 3;
-      e = by_width<T, GatherW>(p->W, a, tile_blocks(p, n), p->stream);
+      bool done = false;
+      if constexpr (sizeof(T) == 8) {
+        if ((done = m64_use(p->W, a.es64))) e = m64_launch(p->W, a, true, tile_blocks(p, n), p->stream);
+      }
+      if (!done) e = by_width<T, GatherW>(p->W, a, tile_blocks(p, n), p->stream);
     }
     if (e == hipSuccess) {
       const int blocks = (int)std::min<int64_t>(8192, (n + 255) / 256);
@@ -1951,6 +1961,7 @@ enufft_status big_prepare(enufft_plan_t p) {
   if (e == hipSuccess)
     e = p->prec == ENUFFT_F64 ? set_attrs_t<double>(g.n1, g.n2, ntiles) : set_attrs_t<float>(g.n1, g.n2, ntiles);
   if (e == hipSuccess) e = p->prec == ENUFFT_F64 ? gather_attrs<double>() : gather_attrs<float>();
+  if (e == hipSuccess && p->prec == ENUFFT_F64) e = m64_attrs();
   if (e == hipSuccess) e = hipDeviceSynchronize();
   return big_fail(p, e, "large-cell workspace");
 }
