@@ -34,7 +34,7 @@ __host__ __device__ inline size_t adj_stage_elems(const Geom &g, size_t elem) {
 // element), so the copy costs about one memory latency instead of one per
 // element.
 template <typename T, int NT>
-__device__ void stage_spectrum(const AdjArgs<T> &a, const T *gc, int cell, T *st) {
+__device__ __forceinline__ void stage_spectrum(const AdjArgs<T> &a, const T *gc, int cell, T *st) {
   const Geom &g = a.g;
   const int M = g.N1 * g.N2, n = 2 * M;
   constexpr int U = 16;
@@ -150,7 +150,7 @@ __device__ __forceinline__ void col_step2_band(const T *col, int cpitch, int k1,
 // spectrum (times i ky with yderiv), formed from the staged copy in the first
 // step and written to the band spectra db by the second.
 template <typename T, int NT>
-__device__ void column_pass(const AdjArgs<T> &a, const T *st, const T *tw2, T two_lam, T *ws, int cpitch,
+__device__ __forceinline__ void column_pass(const AdjArgs<T> &a, const T *st, const T *tw2, T two_lam, T *ws, int cpitch,
                             bool yderiv, T *db, int rows, int y0) {
   const Geom &g = a.g;
   const int per = g.K1 + 1, n2 = g.n2, M = g.N1 * g.N2;
@@ -1124,11 +1124,13 @@ __device__ __forceinline__ void row_step1_staged(int q0, int count, const float 
 // factor -2, so it is not multiplied into every tap.)
 __device__ __forceinline__ void es_pair_dtaps(float u, float s, const float *cd, float &t0, float &t1, float &d0,
                                               float &d1) {
-  float e = cd[ES_DEG - 1], o = cd[ES_DEG], de = 0.0f, dO = 0.0f;
+  float e = cd[ES_DEG - 1], o = cd[ES_DEG], de = e, dO = o;
 #pragma unroll
   for (int k = ES_DEG - 3; k >= 0; k -= 2) {
-    de = fmaf(de, s, e);
-    dO = fmaf(dO, s, o);
+    if (k < ES_DEG - 3) {   // (the first step's derivatives are the leading coefficients)
+      de = fmaf(de, s, e);
+      dO = fmaf(dO, s, o);
+    }
     e = fmaf(e, s, cd[k]);
     o = fmaf(o, s, cd[k + 1]);
   }
@@ -1164,13 +1166,28 @@ __device__ __forceinline__ void hold_rows(float (&ra)[W], float (&rb)[W]) {
   }
 }
 
+// An item's point arrays (at its first point) and the plan's constants of the gather.
+struct Gather1 {
+  const float *x, *y, *h, *w;
+  float *gh, *gx, *gy;
+  float cx, cy, R, pr;
+};
+
+// Element at a 32-bit byte offset of a uniform base (one scalar base, one vector offset).
+__device__ __forceinline__ float at_offset(const float *p, unsigned o) {
+  return *reinterpret_cast<const float *>(reinterpret_cast<const char *>(p) + o);
+}
+__device__ __forceinline__ void put_offset(float *p, unsigned o, float v) {
+  *reinterpret_cast<float *>(reinterpret_cast<char *>(p) + o) = v;
+}
+
 // Gradients at one point: W x W taps of the grid with value and derivative
 // weights (row sums with psi_x and psi_x', then combined with psi_y, psi_y'),
-// then the chain rule through the strength as in gather_point.
-template <int W>
-__device__ __forceinline__ void gather1_point(const AdjArgs<float> &a, const float *G, int apitch, int64_t j, float xj,
-                                              float yj, float hj, float wj, float cx, float cy, float R, float pr) {
-  const Geom &g = a.g;
+// then the chain rule through the strength as in gather_point.  ALL: all three
+// gradients are wanted (no tests per point).
+template <int W, bool ALL>
+__device__ __forceinline__ void gather1_point(const AdjArgs<float> &a, const Gather1 &q, const float *G, int apitch,
+                                              unsigned o, float xj, float yj, float hj, float wj) {
   const float halfw = float(W) * 0.5f;
   const FineCoord<float> fx = fine_coord<float>(xj, a.s1_hi, a.s1_lo, halfw);
   const FineCoord<float> fy = fine_coord<float>(yj, a.s2_hi, a.s2_lo, halfw);
@@ -1178,7 +1195,7 @@ __device__ __forceinline__ void gather1_point(const AdjArgs<float> &a, const flo
   float kx[W], kxd[W];
   es_taps_dtaps_poly_v<W>(vx, a.es, kx, kxd);
   const float uyv = 2.0f * vy - 1.0f, syv = uyv * uyv;
-  const float *p = G + (fy.i0 & (g.n2 - 1)) * apitch + (fx.i0 & (g.n1 - 1));
+  const float *p = G + (fy.i0 & (a.g.n2 - 1)) * apitch + (fx.i0 & (a.g.n1 - 1));
   float u = 0.0f, ux = 0.0f, uy = 0.0f;
   // rows in mirror pairs (d, W - 1 - d), whose y taps come from one polynomial pair
 #pragma unroll
@@ -1193,9 +1210,9 @@ __device__ __forceinline__ void gather1_point(const AdjArgs<float> &a, const flo
     float ta, tb, da, db;
     es_pair_dtaps(uyv, syv, a.es.c + d * (ES_DEG + 1), ta, tb, da, db);
     hold_rows<W>(ra, rb);
-    float sa = 0.0f, sda = 0.0f, sb = 0.0f, sdb = 0.0f;
+    float sa = kx[0] * ra[0], sda = kxd[0] * ra[0], sb = kx[0] * rb[0], sdb = kxd[0] * rb[0];
 #pragma unroll
-    for (int dx = 0; dx < W; ++dx) {
+    for (int dx = 1; dx < W; ++dx) {
       sa = fmaf(kx[dx], ra[dx], sa);
       sda = fmaf(kxd[dx], ra[dx], sda);
       sb = fmaf(kx[dx], rb[dx], sb);
@@ -1214,12 +1231,12 @@ __device__ __forceinline__ void gather1_point(const AdjArgs<float> &a, const flo
   ux *= a.dsx;   // -2 n1 / (2 pi): d/dt of the fine coordinate, d/du = -2 d/dt
   uy *= a.dsy;
   float dWx, dWy;
-  const float Wv = hann_wg(a.window_kind, xj, yj, cx, cy, R, pr, dWx, dWy);
-  if (a.grad_h) a.grad_h[j] = wj * Wv * u;
-  if (a.grad_x || a.grad_y) {
+  const float Wv = hann_wg(a.window_kind, xj, yj, q.cx, q.cy, q.R, q.pr, dWx, dWy);
+  if (ALL || q.gh) put_offset(q.gh, o, wj * Wv * u);
+  if (ALL || q.gx || q.gy) {
     const float wh = wj * hj;
-    if (a.grad_x) a.grad_x[j] = wh * (dWx * u + Wv * ux);
-    if (a.grad_y) a.grad_y[j] = wh * (dWy * u + Wv * uy);
+    if (ALL || q.gx) put_offset(q.gx, o, wh * (dWx * u + Wv * ux));
+    if (ALL || q.gy) put_offset(q.gy, o, wh * (dWy * u + Wv * uy));
   }
 }
 
@@ -1227,37 +1244,38 @@ __device__ __forceinline__ void gather1_point(const AdjArgs<float> &a, const flo
 // lane (so the 64 lanes of a step read overlapping footprints of raster-ordered
 // points); each lane's next point is loaded while the current one is gathered.
 // (Four points per lane and block, picked by a run-time index, had put the
-// buffers in scratch memory: 16 bytes per point written and read back.)
-template <int W, int NT>
-__device__ __forceinline__ void gather1_item(const AdjArgs<float> &a, const float *G, int apitch, int64_t begin,
-                                             int64_t end, float cx, float cy, float R) {
-  const float pr = R > 0.0f ? float(M_PI) / R : 0.0f;
-  constexpr int NWV = NT / 64;
-  const int lane = threadIdx.x & 63;
-  const int64_t stride = (int64_t)NWV * 64;
+// buffers in scratch memory: 16 bytes per point written and read back.)  Indices
+// are 32-bit offsets from the item's first point: with 64-bit point indices each
+// access formed its own address, and with the kernel's arguments held from its start
+// 56 of the loop's 473 vector instructions per point read spilled scalar registers
+// back; both gone, 8,192 triangles of 3.3e8 samples went from 3.83 to 3.41 ms.
+template <int W, int NT, bool ALL>
+__device__ __forceinline__ void gather1_item(const AdjArgs<float> &a, const Gather1 &q, const float *G, int apitch,
+                                             int n) {
+  constexpr int stride = NT;
   struct Pt {
     float x, y, h, w;
   };
-  auto load = [&](Pt &b, int64_t i) {
-    const int64_t ic = i < end ? i : end - 1;   // past the end: re-read the last point (unused)
-    b.x = a.x[ic]; b.y = a.y[ic]; b.h = a.h[ic]; b.w = a.w[ic];
+  auto load = [&](Pt &b, int i) {
+    const unsigned o = 4u * (unsigned)(i < n ? i : n - 1);   // past the end: re-read the last point (unused)
+    b.x = at_offset(q.x, o); b.y = at_offset(q.y, o); b.h = at_offset(q.h, o); b.w = at_offset(q.w, o);
   };
-  if (begin >= end) return;
-  int64_t i = begin + (int64_t)(threadIdx.x >> 6) * 64 + lane;
+  int i = threadIdx.x;
   Pt b0, b1;
   load(b0, i);
-  for (; i - lane < end; i += 2 * stride) {
+  for (; i - (int)(threadIdx.x & 63) < n; i += 2 * stride) {
     load(b1, i + stride);
-    if (i < end) gather1_point<W>(a, G, apitch, i, b0.x, b0.y, b0.h, b0.w, cx, cy, R, pr);
+    if (i < n) gather1_point<W, ALL>(a, q, G, apitch, 4u * (unsigned)i, b0.x, b0.y, b0.h, b0.w);
     load(b0, i + 2 * stride);
-    if (i + stride < end) gather1_point<W>(a, G, apitch, i + stride, b1.x, b1.y, b1.h, b1.w, cx, cy, R, pr);
+    if (i + stride < n) gather1_point<W, ALL>(a, q, G, apitch, 4u * (unsigned)(i + stride), b1.x, b1.y, b1.h, b1.w);
   }
 }
 
 // Four waves per SIMD: two 512-thread workgroups per CU with the compact layout
 // (each thread then within 128 VGPRs).
 template <int W, int NT>
-__global__ __launch_bounds__(NT, (NT == 512 ? 4 : 1)) void adj1_kernel(AdjArgs<float> a) {
+__global__ __launch_bounds__(NT, (NT == 512 ? 4 : 1)) void adj1_kernel(AdjArgs<float>) {
+  const AdjArgs<float> &a = fresh_args<AdjArgs<float>>();
   extern __shared__ __align__(16) unsigned char smem_raw[];
   float *sm = reinterpret_cast<float *>(smem_raw);
   __shared__ int s_item;
@@ -1330,8 +1348,22 @@ __global__ __launch_bounds__(NT, (NT == 512 ? 4 : 1)) void adj1_kernel(AdjArgs<f
     // the first W - 1 rows again after the last (with their repeated columns)
     for (int i = threadIdx.x; i < (W - 1) * pitch; i += NT) G[g.n2 * pitch + i] = G[i];
     __syncthreads();
-    const double *wn = a.windows + 3 * (int64_t)it.cell;
-    gather1_item<W, NT>(a, G, pitch, it.begin, it.end, float(wn[0]), float(wn[1]), float(wn[2]));
+    {
+      const AdjArgs<float> &b = fresh_args<AdjArgs<float>>();
+      const double *wn = b.windows + 3 * (int64_t)it.cell;
+      Gather1 q;
+      q.x = b.x + it.begin; q.y = b.y + it.begin; q.h = b.h + it.begin; q.w = b.w + it.begin;
+      q.gh = b.grad_h ? b.grad_h + it.begin : nullptr;
+      q.gx = b.grad_x ? b.grad_x + it.begin : nullptr;
+      q.gy = b.grad_y ? b.grad_y + it.begin : nullptr;
+      q.cx = float(wn[0]); q.cy = float(wn[1]); q.R = float(wn[2]);
+      q.pr = q.R > 0.0f ? float(M_PI) / q.R : 0.0f;
+      const int n = (int)(it.end - it.begin);
+      if (n > 0) {
+        if (q.gh && q.gx && q.gy) gather1_item<W, NT, true>(b, q, G, pitch, n);
+        else gather1_item<W, NT, false>(b, q, G, pitch, n);
+      }
+    }
     __syncthreads();
   }
   if (threadIdx.x == 0) {
@@ -1388,7 +1420,8 @@ static void build_adj_items(enufft_plan_t p, int64_t c0, int64_t c1, int slots, 
                             std::vector<AdjItem> &items) {
   const int64_t Q = p->offsets[c1] - p->offsets[c0];
   const int64_t per = (int64_t)p->adj_items_per_slot * std::max(1, slots);
-  const int64_t T = std::max<int64_t>(least * B, (Q * B + per - 1) / per);
+  // (at most 2^28 points: the gathers' offsets inside an item are 32-bit)
+  const int64_t T = std::min<int64_t>(std::max<int64_t>(least * B, (Q * B + per - 1) / per), int64_t(1) << 28);
   const size_t first = items.size();
   for (int64_t c = c0; c < c1; ++c) {
     const int64_t a = p->offsets[c], b = p->offsets[c + 1];

@@ -119,6 +119,19 @@ struct AdjArgs {
   Geom g;
 };
 
+// The kernel's argument block (its only parameter, at the start of the kernel argument
+// segment), read anew: the loads that follow are scalar and belong to the phase that
+// makes them, where the by-value parameter's fields are all loaded at the kernel's
+// start and held in scalar registers to its end (spilled to vector lanes, one lane move
+// per use, in kernels of several phases).
+template <typename Args>
+__device__ __forceinline__ const Args &fresh_args() {
+  typedef const Args __attribute__((address_space(4))) *Ptr;
+  Ptr p = (Ptr)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(p));
+  return *(const Args *)p;
+}
+
 // ------------------------------------------------------------------ ES kernel
 
 // psi(z) = exp(beta (sqrt(1 - z^2) - 1)) on |z| <= 1, evaluated as
