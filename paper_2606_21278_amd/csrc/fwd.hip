@@ -269,10 +269,108 @@ __device__ __forceinline__ void drain_groups(const FwdArgs<T> &a, A *grid, const
   }
 }
 
+// FP64 points with the kernel polynomial, W > 8: a wave loads 64 points and spreads four
+// at a time, one per row of sixteen lanes.  Lane d of a row evaluates tap d of its
+// point along both axes (its own pair's coefficients, held in registers), and the
+// footprint goes out one grid row per instruction: the y tap of row r is broadcast from
+// lane r of the row, and the W lanes add to W consecutive cells.  With one point per
+// lane the 64 adds of an instruction fell on unrelated banks, and the conflicts made an
+// add cost three times the 8.7 cycles of one without: 57 cycles per point of a CU at
+// W = 12, here 41 (the adds of four twelve-cell segments, 13.7 cycles each); 64 cells of
+// 2.1e6 points went from 467 to 292 us.  Up to W = 8 half the lanes would idle, and the
+// points are spread one per lane.
+template <int L, typename V>
+__device__ __forceinline__ V row_bcast(V v) {   // lane L of each row of sixteen
+  return __builtin_amdgcn_mov_dpp(v, 0x150 + L, 0xf, 0xf, true);
+}
+__device__ __forceinline__ int row_next4(int v) {   // lane i takes lane i + 4 of its row
+  return __builtin_amdgcn_mov_dpp(v, 0x120 + 12, 0xf, 0xf, true);
+}
+__device__ __forceinline__ double row_next4(double v) {
+  return __hiloint2double(row_next4(__double2hiint(v)), row_next4(__double2loint(v)));
+}
+
+template <int W>
+struct RowTap {
+  double e[(ES64_DEG + 1) / 2], o[(ES64_DEG + 1) / 2];   // even and (signed) odd coefficients of the lane's tap
+  __device__ __forceinline__ void init(const EsPoly64 &cf, int li) {
+    const bool m = li >= W / 2;
+    const double *c = cf.c + (m ? max(W - 1 - li, 0) : li) * (ES64_DEG + 1);
+#pragma unroll
+    for (int k = 0; k < (ES64_DEG + 1) / 2; ++k) {
+      e[k] = c[2 * k];
+      o[k] = m ? -c[2 * k + 1] : c[2 * k + 1];
+    }
+  }
+  __device__ __forceinline__ double operator()(double u) const {   // as poly64_pair_eval
+    constexpr int H = (ES64_DEG + 1) / 2;
+    const double s = u * u;
+    double pe = e[H - 1], po = o[H - 1];
+#pragma unroll
+    for (int k = H - 2; k >= 0; --k) {
+      pe = fma(pe, s, e[k]);
+      po = fma(po, s, o[k]);
+    }
+    return fma(u, po, pe);
+  }
+};
+
+// The rows R .. W - 1 of one point's footprint (p: the lane's cell in row R).
+template <int W, int R = 0>
+__device__ __forceinline__ void add_rows(double *p, int pitch, double kx, double cky) {
+  if constexpr (R < W) {
+    __hip_atomic_fetch_add(p, row_bcast<R>(cky) * kx, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    add_rows<W, R + 1>(p + pitch, pitch, kx, cky);
+  }
+}
+// The points of lanes L .. 3 of each row; o: the origin's row offset and column, -1 for
+// a point that adds nothing.
+template <int W, int L = 0>
+__device__ __forceinline__ void add_points(const Geom &g, double *grid, int pitch, const RowTap<W> &tap, int li, double ux,
+                                           double uy, double c, int o) {
+  if constexpr (L < 4) {
+    const int op = row_bcast<L>(o);
+    const double vx = row_bcast<L>(ux), vy = row_bcast<L>(uy), cp = row_bcast<L>(c);
+    if (op >= 0 && li < W) {
+      const double kx = tap(vx), cky = cp * tap(vy);
+      add_rows<W>(grid + (op >> 8) + (((op & 0xff) + li) & (g.n1 - 1)), pitch, kx, cky);
+    }
+    add_points<W, L + 1>(g, grid, pitch, tap, li, ux, uy, c, o);
+  }
+}
+
+template <int W, int NT>
+__device__ __forceinline__ void spread_rows(const FwdArgs<double> &a, double *grid, int64_t begin, int64_t end, double cx,
+                                            double cy, double R) {
+  const Geom &g = a.g;
+  const int pitch = g.pitch, lane = threadIdx.x & 63, li = lane & 15;
+  const double halfw = double(W) * 0.5, pr = R > 0.0 ? M_PI / R : 0.0;
+  RowTap<W> tap;
+  tap.init(a.es64, li);
+  for (int64_t b = begin + (threadIdx.x & ~63); b < end; b += NT) {
+    const int64_t j = min(b + lane, end - 1);
+    const double xj = a.x[j], yj = a.y[j];
+    const double c = b + lane < end ? a.w[j] * a.h[j] * hann_w(a.window_kind, xj, yj, cx, cy, R, pr) : 0.0;
+    const FineCoord<double> fx = fine_coord<double>(xj, a.s1_hi, a.s1_lo, halfw);
+    const FineCoord<double> fy = fine_coord<double>(yj, a.s2_hi, a.s2_lo, halfw);
+    double ux = tap_u64(fx, halfw), uy = tap_u64(fy, halfw), cc = c;
+    int o = c == 0.0 ? -1 : ((fy.i0 & (g.n2 - 1)) * pitch) << 8 | (fx.i0 & (g.n1 - 1));
+#pragma unroll 1
+    for (int q = 0; q < 4; ++q) {
+      add_points<W>(g, grid, pitch, tap, li, ux, uy, cc, o);
+      ux = row_next4(ux); uy = row_next4(uy); cc = row_next4(cc); o = row_next4(o);
+    }
+  }
+}
+
 // Spread the points [begin, end) of one item into the LDS grid.
 template <typename T, typename A, int W, int NT, int P>
 __device__ __forceinline__ void spread_item(const FwdArgs<T> &a, A *grid, int *queue, int64_t begin,
                                             int64_t end, T cx, T cy, T R) {
+  if constexpr (sizeof(T) == 8 && P != 0 && W > 8) {
+    spread_rows<W, NT>(a, grid, begin, end, cx, cy, R);
+    return;
+  }
   const T halfw = T(W) / T(2);
   const T pr = R > T(0) ? T(M_PI) / R : T(0);
   int64_t body0 = end, body1 = end;
