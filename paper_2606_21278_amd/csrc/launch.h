@@ -13,6 +13,9 @@ hipError_t launch_fwd(const FwdArgs<T> &a, int W, int blocks, int threads, size_
 template <typename T>
 hipError_t fwd_occupancy(int W, int threads, int pitch, int acc, size_t lds, int *blocks_per_cu);
 
+// Bytes of the allocation-free entry's fixed scratch array.
+constexpr size_t kNoallocScratch = size_t(64) << 20;
+
 // Per-wave queue of deferred point groups in the forward kernel (entries).
 constexpr int FWD_QCAP = 128;
 // Row pitch of the 128-wide fine grid (64-mode boxes at sigma 2), for which

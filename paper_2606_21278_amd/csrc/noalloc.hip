@@ -20,7 +20,7 @@ namespace {
 // The scratch array: one copy per GPU, held until the process ends.  In host
 // code its name stands for the device symbol, not an address; the address of
 // each device's copy comes from hipGetSymbolAddress and is kept per device.
-constexpr size_t kScratchBytes = size_t(64) << 20;
+constexpr size_t kScratchBytes = kNoallocScratch;
 __device__ __align__(256) unsigned char scratch[kScratchBytes];
 
 constexpr int kMaxDevices = 64;

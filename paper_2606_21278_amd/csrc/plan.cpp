@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <functional>
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
@@ -356,10 +357,54 @@ void dev_release(enufft_plan_t p, void **ptr, size_t bytes) {
 // fixed costs, zeroing, folding and writing a whole grid, outweigh its points).
 constexpr int64_t kPercellChunkMin = 4096;
 
+// Chunk size of an FP64 plan whose user and tuner named none.  Below 16,384 points a
+// chunk pays as long as workgroups would idle: the sizes from T down to 512 points are
+// compared by the end of a longest-first schedule, in points of spreading time (41
+// cycles each): an item's zeroing, folding and transform are about 800 points on a 128^2
+// grid, a split cell's exchange another 300 per chunk and 40 per chunk of the cell for
+// its last one.  64 cells of 2.1e6 points: 160 chunks of at most 16,384 to 248, the
+// forward kernel 292 to 233 us; one cell of 2,000 points: one chunk to four, 37 us to 23.
+// A smaller chunk is taken only while the partial grids stay within the allocation-free
+// entry's scratch.  FP32 plans keep the larger chunks: their partial grids are rounded to
+// FP32, so a finer split would change the results.
+static int64_t f64_chunk(enufft_plan_t p, int slots, int64_t T) {
+  if (p->n_cells > 2 * (int64_t)slots || slots < 1) return T;
+  const int64_t nn = (int64_t)p->n1 * p->n2;
+  const int64_t fix = 800 * nn / 16384, part = 300 * nn / 16384, sum = std::max<int64_t>(10, 40 * nn / 16384);
+  const size_t room = kNoallocScratch / 2 / ((size_t)nn * p->elem);
+  int64_t best = T, best_end = -1;
+  std::vector<int64_t> cost, end;
+  for (int64_t t = T; t >= 512; t = t * 7 / 8) {
+    cost.clear();
+    size_t parts = 0;
+    for (int64_t c = 0; c < p->n_cells; ++c) {
+      const int64_t q = p->offsets[c + 1] - p->offsets[c], nch = std::max<int64_t>(1, (q + t - 1) / t);
+      for (int64_t i = 0; i < nch; ++i)
+        cost.push_back(fix + (q + nch - 1) / nch + (nch > 1 ? part : 0) + (nch > 1 && i == 0 ? sum * nch : 0));
+      if (nch > 1) parts += (size_t)nch;
+    }
+    if (t < T && parts > room) break;
+    std::sort(cost.begin(), cost.end(), std::greater<int64_t>());
+    end.assign((size_t)slots, 0);   // min-heap of the workgroups' ends
+    for (int64_t v : cost) {
+      std::pop_heap(end.begin(), end.end(), std::greater<int64_t>());
+      end.back() += v;
+      std::push_heap(end.begin(), end.end(), std::greater<int64_t>());
+    }
+    const int64_t last = *std::max_element(end.begin(), end.end());
+    if (best_end < 0 || last < best_end) {
+      best_end = last;
+      best = t;
+    }
+  }
+  return best;
+}
+
 void build_fwd_schedule(enufft_plan_t p, int slots) {
   const int64_t Q = p->n_points;
   const int64_t per = (int64_t)p->fwd_items_per_slot * std::max(1, slots);
-  const int64_t T = std::max<int64_t>(p->fwd_chunk_min, (Q + per - 1) / per);
+  int64_t T = std::max<int64_t>(p->fwd_chunk_min, (Q + per - 1) / per);
+  if (p->prec == ENUFFT_F64 && p->fwd_chunk_auto) T = f64_chunk(p, slots, T);
   p->fwd_items.clear();
   p->fwd_items_cell.clear();
   p->fwd_cell_first.assign(p->n_cells + 1, 0);
@@ -644,8 +689,14 @@ enufft_status enufft_plan(enufft_plan_t *out, int64_t n_cells, const int64_t *ce
     int threads = 512;
     if (const char *ev = std::getenv("ENUFFT_FWD_THREADS")) threads = std::atoi(ev);
     if (const char *ev = std::getenv("ENUFFT_FWD_ACC")) p->fwd_acc = std::atoi(ev) == 4 ? 4 : 8;
-    if (const char *ev = std::getenv("ENUFFT_FWD_CHUNK_MIN")) p->fwd_chunk_min = std::max(1024LL, std::atoll(ev));
-    if (const char *ev = std::getenv("ENUFFT_FWD_ITEMS_PER_SLOT")) p->fwd_items_per_slot = std::max(1, std::atoi(ev));
+    if (const char *ev = std::getenv("ENUFFT_FWD_CHUNK_MIN")) {
+      p->fwd_chunk_min = std::max(1024LL, std::atoll(ev));
+      p->fwd_chunk_auto = false;
+    }
+    if (const char *ev = std::getenv("ENUFFT_FWD_ITEMS_PER_SLOT")) {
+      p->fwd_items_per_slot = std::max(1, std::atoi(ev));
+      p->fwd_chunk_auto = false;
+    }
     st = enufft::set_fwd_threads(p, threads, (size_t)prop.sharedMemPerBlock);
     if (st != ENUFFT_OK) { std::string m = p->last_error; free_plan(p); return fail(nullptr, st, m); }
   }

@@ -237,6 +237,7 @@ enufft_status run_trials(enufft_plan_t t, size_t lds_limit, int unordered, Choic
     for (int64_t cm : {4096LL, 16384LL, 65536LL}) {
       for (int ips : {1, 2, 4}) {
         t->fwd_chunk_min = cm;
+        t->fwd_chunk_auto = false;
         t->fwd_items_per_slot = ips;
         st = install_fwd_schedule(t);
         if (st != ENUFFT_OK) break;
@@ -257,6 +258,7 @@ enufft_status run_trials(enufft_plan_t t, size_t lds_limit, int unordered, Choic
   if (st == ENUFFT_OK) st = set_fwd_threads(t, c.fwd_threads, lds_limit);
   if (st == ENUFFT_OK) {
     t->fwd_chunk_min = c.chunk_min;
+    t->fwd_chunk_auto = false;
     t->fwd_items_per_slot = c.fwd_ips;
     st = install_fwd_schedule(t);
   }
@@ -330,6 +332,7 @@ enufft_status autotune(enufft_plan_t p) {
   enufft_status st = set_fwd_threads(p, c.fwd_threads, (size_t)prop.sharedMemPerBlock);
   if (st != ENUFFT_OK) return st;
   p->fwd_chunk_min = c.chunk_min;
+  p->fwd_chunk_auto = false;
   p->fwd_items_per_slot = c.fwd_ips;
   p->adj_items_per_slot = c.adj_ips;
   p->adj1 = p->adj1_avail && c.band_mult == 0;
