@@ -412,6 +412,30 @@ __host__ __device__ inline BandLayout band_layout(const Geom &g, int W, int band
   return L;
 }
 
+// What a point's interpolated u (and du/dx, du/dy) gives: the gradients, or in the
+// reconstruction mode the error sums.
+template <typename T, bool RECON>
+__device__ __forceinline__ void finish_point(const AdjArgs<T> &a, int64_t j, T xj, T yj, T hj, T wj, T cx, T cy, T R, T pr,
+                                             T u, T ux, T uy, double (&acc)[3]) {
+  if constexpr (RECON) {
+    const double t = (double)(hj * hann_w(a.window_kind, xj, yj, cx, cy, R, pr));
+    const double d = t - (double)u;
+    acc[0] += d * d;
+    acc[1] += t * t;
+    acc[2] += (double)wj * t * t;
+    if (a.grad_h) a.grad_h[j] = u;
+    return;
+  }
+  T dWx, dWy;
+  const T Wv = hann_wg(a.window_kind, xj, yj, cx, cy, R, pr, dWx, dWy);
+  if (a.grad_h) a.grad_h[j] = wj * Wv * u;
+  if (a.grad_x || a.grad_y) {
+    const T wh = wj * hj;
+    if (a.grad_x) a.grad_x[j] = wh * (dWx * u + Wv * ux);
+    if (a.grad_y) a.grad_y[j] = wh * (dWy * u + Wv * uy);
+  }
+}
+
 // Gradients at one point whose footprint starts in band row r0, from the band's
 // three grids (W x W taps each); the chain rule through the strength
 // c_j = w_j W(x_j) h_j turns the interpolated u, du/dx, du/dy into dL/dh,
@@ -486,22 +510,106 @@ __device__ __forceinline__ void gather_point(const AdjArgs<T> &a, const T *G, co
 #pragma unroll 1
     for (int dy = 0; dy < W; ++dy) row(dy, ker_eval(fy.offset(dy) * zsc, a.beta));
   }
-  if constexpr (RECON) {
-    const double t = (double)(hj * hann_w(a.window_kind, xj, yj, cx, cy, R, pr));
-    const double d = t - (double)u;
-    acc[0] += d * d;
-    acc[1] += t * t;
-    acc[2] += (double)wj * t * t;
-    if (a.grad_h) a.grad_h[j] = u;
-    return;
+  finish_point<T, RECON>(a, j, xj, yj, hj, wj, cx, cy, R, pr, u, ux, uy, acc);
+}
+
+// FP64 with the kernel polynomial, W > 8: the points of a wave's lanes, four at a time,
+// one per row of sixteen lanes.  Lane d of a row evaluates tap d of its point along both
+// axes and sums its column down the W rows (the y taps broadcast along the row), so an
+// instruction reads W consecutive cells per point; one point per lane read 64 unrelated
+// ones, two thirds of whose LDS cycles were bank conflicts.  The column sums times
+// their x taps are then added up within the row.  64 cells of 2.1e6 points at W = 12: 324
+// to 304 us (60 cycles per point of a CU, its arithmetic and its LDS reads half each;
+// 13 % are the bands' row transforms and a quarter the uneven bands of 2.5 items per CU).
+//
+// The row sums of four points are merged as they are halved: after two steps each
+// quarter of a row holds one point's, at the cost of 1.7 plain reductions instead of 4.
+template <int N>
+__device__ __forceinline__ double row_ror(double v) {   // lane i takes lane (i - N) mod 16 of its row
+  return __hiloint2double(__builtin_amdgcn_mov_dpp(__double2hiint(v), 0x120 + N, 0xf, 0xf, true),
+                          __builtin_amdgcn_mov_dpp(__double2loint(v), 0x120 + N, 0xf, 0xf, true));
+}
+template <int X>
+__device__ __forceinline__ double quad_xor(double v) {   // lane i takes lane i ^ X of its quad
+  constexpr int P = X == 1 ? 0xb1 : 0x4e;                // quad_perm [1,0,3,2] or [2,3,0,1]
+  return __hiloint2double(__builtin_amdgcn_mov_dpp(__double2hiint(v), P, 0xf, 0xf, true),
+                          __builtin_amdgcn_mov_dpp(__double2loint(v), P, 0xf, 0xf, true));
+}
+// The rows of a lane's column, the y tap of row R from lane R of its row.
+template <int W, bool RECON, int R = 0>
+__device__ __forceinline__ void column_rows(const double2 *q, const double *qy, int apitch, double ky, double (&s)[3]) {
+  if constexpr (R < W) {
+    const double k = row_bcast<R>(ky);
+    if constexpr (RECON) {
+      s[0] = fma(k, *qy, s[0]);
+    } else {
+      const double2 v = *q;
+      s[0] = fma(k, v.x, s[0]);
+      s[1] = fma(k, v.y, s[1]);
+      s[2] = fma(k, *qy, s[2]);
+    }
+    column_rows<W, RECON, R + 1>(q + apitch, qy + apitch, apitch, ky, s);
   }
-  T dWx, dWy;
-  const T Wv = hann_wg(a.window_kind, xj, yj, cx, cy, R, pr, dWx, dWy);
-  if (a.grad_h) a.grad_h[j] = wj * Wv * u;
-  if (a.grad_x || a.grad_y) {
-    const T wh = wj * hj;
-    if (a.grad_x) a.grad_x[j] = wh * (dWx * u + Wv * ux);
-    if (a.grad_y) a.grad_y[j] = wh * (dWy * u + Wv * uy);
+}
+// Quarters of a row afterwards: the sums of v[0], v[2], v[1], v[3], in all their lanes.
+__device__ __forceinline__ double row_sums4(const double (&v)[4], int li) {
+  const bool up = li & 8, odd = li & 4;
+  const double t0 = (up ? v[1] : v[0]) + row_ror<8>(up ? v[0] : v[1]);
+  const double t1 = (up ? v[3] : v[2]) + row_ror<8>(up ? v[2] : v[3]);
+  const double send = odd ? t0 : t1;
+  const double below = row_ror<4>(send), above = row_ror<12>(send);   // both in every lane
+  double r = (odd ? t1 : t0) + (odd ? below : above);
+  r += quad_xor<1>(r);
+  r += quad_xor<2>(r);
+  return r;
+}
+template <int W, bool RECON, int L = 0>
+__device__ __forceinline__ void row_points(const double *G, const double *Gy, int apitch, const RowTap<W> &tap, int li,
+                                           double ux, double uy, int o, double (&su)[4], double (&sx)[4],
+                                           double (&sy)[4]) {
+  if constexpr (L < 4) {
+    const int op = row_bcast<L>(o);
+    const double vx = row_bcast<L>(ux), vy = row_bcast<L>(uy);
+    su[L] = sx[L] = sy[L] = 0.0;
+    if (op >= 0 && li < W) {
+      const double kx = tap(vx), ky = tap(vy);
+      double s[3] = {0.0, 0.0, 0.0};
+      column_rows<W, RECON>(reinterpret_cast<const double2 *>(G) + op + li, (RECON ? G : Gy) + op + li, apitch, ky, s);
+      su[L] = kx * s[0];
+      if constexpr (!RECON) {
+        sx[L] = kx * s[1];
+        sy[L] = kx * s[2];
+      }
+    }
+    row_points<W, RECON, L + 1>(G, Gy, apitch, tap, li, ux, uy, o, su, sx, sy);
+  }
+}
+// e: the first element of the lane's own point, -1 for none.  The lane's u, ux, uy.
+template <int W, bool RECON>
+__device__ __forceinline__ void gather_rows(const double *G, const double *Gy, int apitch, const RowTap<W> &tap, double ux,
+                                            double uy, int e, double &u, double &gx, double &gy) {
+  const int lane = threadIdx.x & 63, li = lane & 15;
+  double ru = 0.0, rx = 0.0, ry = 0.0;
+#pragma unroll 1
+  for (int q = 0; q < 4; ++q) {
+    double su[4], sx[4], sy[4];
+    row_points<W, RECON>(G, Gy, apitch, tap, li, ux, uy, e, su, sx, sy);
+    const double tu = row_sums4(su, li);
+    const bool mine = (li & 3) == q;   // lane 4 k + q of a row keeps quarter k's sums of round q
+    ru = mine ? tu : ru;
+    if constexpr (!RECON) {
+      const double tx = row_sums4(sx, li), ty = row_sums4(sy, li);
+      rx = mine ? tx : rx;
+      ry = mine ? ty : ry;
+    }
+    ux = row_next4(ux); uy = row_next4(uy); e = row_next4(e);
+  }
+  // the point of lane 4 q + L: quarter L (1 and 2 exchanged), its lane q
+  const int L = li & 3, src = (lane & 48) + 4 * (L == 1 ? 2 : L == 2 ? 1 : L) + (li >> 2);
+  u = __shfl(ru, src, 64);
+  if constexpr (!RECON) {
+    gx = __shfl(rx, src, 64);
+    gy = __shfl(ry, src, 64);
   }
 }
 
@@ -521,6 +629,19 @@ __device__ __forceinline__ void gather_item(const AdjArgs<T> &a, const T *G, con
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int mask2 = a.g.n2 - 1;
   if (begin >= end) return;
+  constexpr bool kRows = POLY && sizeof(T) == 8 && W > 8;
+  typename std::conditional<kRows, RowTap<W>, int>::type tap;
+  if constexpr (kRows) tap.init(a.es64, lane & 15);
+  // the whole wave: point j per lane (on: a point at all), its footprint from row r0 of G
+  auto rows = [&](bool on, int64_t j, T xj, T yj, T hj, T wj, int lo) {
+    if constexpr (kRows) {
+      const FineCoord<T> fx = fine_coord<T>(xj, a.s1_hi, a.s1_lo, halfw), fy = fine_coord<T>(yj, a.s2_hi, a.s2_lo, halfw);
+      const int e = on ? ((fy.i0 & mask2) - lo) * apitch + (fx.i0 & (a.g.n1 - 1)) : -1;
+      T u = 0, ux = 0, uy = 0;
+      gather_rows<W, RECON>(G, Gy, apitch, tap, tap_u64(fx, halfw), tap_u64(fy, halfw), e, u, ux, uy);
+      if (on) finish_point<T, RECON>(a, j, xj, yj, hj, wj, cx, cy, R, pr, u, ux, uy, acc);
+    }
+  };
   if (a.band_rows > mask2) {
     struct Pt {
       T x, y, h, w;
@@ -530,7 +651,9 @@ __device__ __forceinline__ void gather_item(const AdjArgs<T> &a, const T *G, con
       b.x = a.x[ic]; b.y = a.y[ic]; b.h = a.h[ic]; b.w = a.w[ic];
     };
     auto step = [&](const Pt &b, int64_t i) {
-      if (i < end) {
+      if constexpr (kRows) {
+        rows(i < end, i, b.x, b.y, b.h, b.w, 0);
+      } else if (i < end) {
         const FineCoord<T> fy = fine_coord<T>(b.y, a.s2_hi, a.s2_lo, halfw);
         gather_point<T, W, POLY, RECON>(a, G, Gy, apitch, fy.i0 & mask2, fy, i, b.x, b.y, b.h, b.w, cx, cy, R, pr,
                                         acc);
@@ -551,7 +674,11 @@ __device__ __forceinline__ void gather_item(const AdjArgs<T> &a, const T *G, con
   constexpr int U = 4, BLK = 64 * U;
   int *wq = queue + wave * ADJ_QCAP;
   auto drain = [&](int n) {
-    if (lane < n) {
+    if constexpr (kRows) {   // neighbours of the queue in different rows, so a short one fills all
+      const int k = (lane & 15) * 4 + (lane >> 4);
+      const int64_t j = begin + wq[min(k, n - 1)];
+      rows(k < n, j, a.x[j], a.y[j], a.h[j], a.w[j], band_lo);
+    } else if (lane < n) {
       const int64_t j = begin + wq[lane];
       const T xj = a.x[j], yj = a.y[j], hj = a.h[j], wj = a.w[j];
       const FineCoord<T> fy = fine_coord<T>(yj, a.s2_hi, a.s2_lo, halfw);
@@ -605,7 +732,7 @@ __device__ __forceinline__ void gather_item(const AdjArgs<T> &a, const T *G, con
     }
   }
   order();
-  drain(nq);
+  if (nq > 0) drain(nq);
 }
 
 template <typename T, int W, int NT, bool POLY, bool RECON>

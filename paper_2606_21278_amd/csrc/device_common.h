@@ -373,6 +373,44 @@ __device__ __forceinline__ void es_taps_poly64(double u, const EsPoly64 &cf, dou
   for (int d = 0; d < W / 2; ++d) poly64_pair_eval(poly64_pair(cf, d), u, s, out[d], out[W - 1 - d]);
 }
 
+// Rows of sixteen lanes with one point each (FP64, W > 8): lane d of a row holds tap d of
+// its point.
+template <int L, typename V>
+__device__ __forceinline__ V row_bcast(V v) {   // lane L of each row of sixteen
+  return __builtin_amdgcn_mov_dpp(v, 0x150 + L, 0xf, 0xf, true);
+}
+__device__ __forceinline__ int row_next4(int v) {   // lane i takes lane i + 4 of its row
+  return __builtin_amdgcn_mov_dpp(v, 0x120 + 12, 0xf, 0xf, true);
+}
+__device__ __forceinline__ double row_next4(double v) {
+  return __hiloint2double(row_next4(__double2hiint(v)), row_next4(__double2loint(v)));
+}
+
+template <int W>
+struct RowTap {
+  double e[(ES64_DEG + 1) / 2], o[(ES64_DEG + 1) / 2];   // even and (signed) odd coefficients of the lane's tap
+  __device__ __forceinline__ void init(const EsPoly64 &cf, int li) {
+    const bool m = li >= W / 2;
+    const double *c = cf.c + (m ? max(W - 1 - li, 0) : li) * (ES64_DEG + 1);
+#pragma unroll
+    for (int k = 0; k < (ES64_DEG + 1) / 2; ++k) {
+      e[k] = c[2 * k];
+      o[k] = m ? -c[2 * k + 1] : c[2 * k + 1];
+    }
+  }
+  __device__ __forceinline__ double operator()(double u) const {   // as poly64_pair_eval
+    constexpr int H = (ES64_DEG + 1) / 2;
+    const double s = u * u;
+    double pe = e[H - 1], po = o[H - 1];
+#pragma unroll
+    for (int k = H - 2; k >= 0; --k) {
+      pe = fma(pe, s, e[k]);
+      po = fma(po, s, o[k]);
+    }
+    return fma(u, po, pe);
+  }
+};
+
 // One tap, dd in [0, W): Horner on its pair's coefficients at +-u (dd uniform
 // across the wave, so the coefficient loads stay scalar).
 template <int W>

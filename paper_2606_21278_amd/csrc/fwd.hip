@@ -279,42 +279,6 @@ __device__ __forceinline__ void drain_groups(const FwdArgs<T> &a, A *grid, const
 // W = 12, here 41 (the adds of four twelve-cell segments, 13.7 cycles each); 64 cells of
 // 2.1e6 points went from 467 to 292 us.  Up to W = 8 half the lanes would idle, and the
 // points are spread one per lane.
-template <int L, typename V>
-__device__ __forceinline__ V row_bcast(V v) {   // lane L of each row of sixteen
-  return __builtin_amdgcn_mov_dpp(v, 0x150 + L, 0xf, 0xf, true);
-}
-__device__ __forceinline__ int row_next4(int v) {   // lane i takes lane i + 4 of its row
-  return __builtin_amdgcn_mov_dpp(v, 0x120 + 12, 0xf, 0xf, true);
-}
-__device__ __forceinline__ double row_next4(double v) {
-  return __hiloint2double(row_next4(__double2hiint(v)), row_next4(__double2loint(v)));
-}
-
-template <int W>
-struct RowTap {
-  double e[(ES64_DEG + 1) / 2], o[(ES64_DEG + 1) / 2];   // even and (signed) odd coefficients of the lane's tap
-  __device__ __forceinline__ void init(const EsPoly64 &cf, int li) {
-    const bool m = li >= W / 2;
-    const double *c = cf.c + (m ? max(W - 1 - li, 0) : li) * (ES64_DEG + 1);
-#pragma unroll
-    for (int k = 0; k < (ES64_DEG + 1) / 2; ++k) {
-      e[k] = c[2 * k];
-      o[k] = m ? -c[2 * k + 1] : c[2 * k + 1];
-    }
-  }
-  __device__ __forceinline__ double operator()(double u) const {   // as poly64_pair_eval
-    constexpr int H = (ES64_DEG + 1) / 2;
-    const double s = u * u;
-    double pe = e[H - 1], po = o[H - 1];
-#pragma unroll
-    for (int k = H - 2; k >= 0; --k) {
-      pe = fma(pe, s, e[k]);
-      po = fma(po, s, o[k]);
-    }
-    return fma(u, po, pe);
-  }
-};
-
 // The rows R .. W - 1 of one point's footprint (p: the lane's cell in row R).
 template <int W, int R = 0>
 __device__ __forceinline__ void add_rows(double *p, int pitch, double kx, double cky) {
