@@ -686,7 +686,16 @@ enufft_status enufft_plan(enufft_plan_t *out, int64_t n_cells, const int64_t *ce
   // ---- forward launch shape (threads per workgroup: ENUFFT_FWD_THREADS, or the autotuner)
   enufft_status st = ENUFFT_OK;
   if (!big) {
+    // Sixteen waves per CU hide the FP32 runs' latency better than eight (20,480 triangles
+    // of 40,000 points on the 128-wide grid: 7.57 ms at 512 threads, 7.15 at 1,024; 3,000
+    // of them 972 to 918 us, 4,000 hexagons of 30,000 points in no order 3,045 to 3,031),
+    // but their 128 registers spill beside the runs, which shows where a cell's points
+    // do not outweigh its transform (4,000 cells of 600 points: 336 us against 350) or a
+    // workgroup takes few cells (1,500 of 3,300 points: 185 against 197).
     int threads = 512;
+    if (p->prec == ENUFFT_F32 && W <= 6 && p->es.on && g.pitch == enufft::FWD_PITCH128 &&
+        n_cells >= 8 * (int64_t)p->n_cu && p->n_points >= 8192 * (int64_t)n_cells)
+      threads = 1024;
     if (const char *ev = std::getenv("ENUFFT_FWD_THREADS")) threads = std::atoi(ev);
     if (const char *ev = std::getenv("ENUFFT_FWD_ACC")) p->fwd_acc = std::atoi(ev) == 4 ? 4 : 8;
     if (const char *ev = std::getenv("ENUFFT_FWD_CHUNK_MIN")) {
