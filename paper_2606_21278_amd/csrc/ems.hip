@@ -572,16 +572,20 @@ __global__ __launch_bounds__(64 * NW, (ems_min_waves<NW>())) void ems_kernel(Ems
   const double run0 = block_exclusive_scan<NW, double>(loc, red1, wave, lane);
   int kc = INT_MAX;
   // (a division only near the crossing: below `under` the quotient is short of alpha_C;
-  // non-negative energies cross once, in the one thread whose sums straddle it)
+  // non-negative energies cross a positive alpha_C once, in the one thread whose sums
+  // straddle it.  alpha_C <= 0, where alpha_min > alpha_max and C > 1, is met by the first
+  // position and straddled by no thread's sums: there, and with negative weighted
+  // energies, every position is divided)
+  const bool every = kmin < 0 || !(alphaC > 0.0);
   const double under = alphaC * T1 * (1.0 - 1e-12), over = alphaC * T1 * (1.0 + 1e-12);
-  if (T1 > 0.0 && t * R < J && (kmin < 0 || (run0 + loc >= under && run0 <= over))) {
+  if (T1 > 0.0 && t * R < J && (every || (run0 + loc >= under && run0 <= over))) {
     double v[R], run = run0;
 #pragma unroll
     for (int r = 0; r < R; ++r) v[r] = sorted[ems_sidx(t * R + r)];
 #pragma unroll
     for (int r = 0; r < R; ++r) {
       run += v[r];
-      if (kc == INT_MAX && t * R + r < J && !(run < under) && run / T1 >= alphaC) kc = t * R + r + 1;
+      if (kc == INT_MAX && t * R + r < J && (every || !(run < under)) && run / T1 >= alphaC) kc = t * R + r + 1;
     }
   }
   kc = block_min_i<NW>(kc, redi0, wave);
