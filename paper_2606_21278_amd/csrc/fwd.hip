@@ -617,8 +617,11 @@ __device__ void fft_deconv_store(const FwdArgs<T> &a, T *G, int cell) {
 //
 // The slots are exchanged between workgroups of different XCDs, whose L2 caches are not
 // coherent: releasing a plain store writes back a whole L2.  The slots are therefore
-// written through it in 8-byte units, and one thread releases for the workgroup behind
-// the barrier.  With plain stores and a release by every wave a chunk (13,000 points of a
+// written through it in 8-byte units.  Every wave waits until its own stores have
+// arrived (a barrier does not wait for them, and the release of one wave waits for that
+// wave's only), and one thread releases for the workgroup behind the barrier.  In the
+// workgroup that sums, every wave acquires for itself.
+// With plain stores and a release by every wave a chunk (13,000 points of a
 // 128^2 FP32 grid on average) spent 87,000 of its 324,000 cycles here, now 15,000: 256
 // cells of 8.4e6 points went from 432 to 312 us, 12 cells from 84 to 74.
 template <typename T, int NT>
@@ -635,16 +638,18 @@ __device__ __forceinline__ bool merge_chunks(const FwdArgs<T> &a, T *G, const Fw
   for (int u = threadIdx.x; u < nu; u += NT)
     __hip_atomic_store(slot + u, *reinterpret_cast<const unsigned long long *>(G + at(u)), __ATOMIC_RELAXED,
                        __HIP_MEMORY_SCOPE_AGENT);
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
   if (threadIdx.x == 0) {
     __threadfence();
     const int old = atomicAdd(a.cell_counters + it.cell, 1);
     *last = old == it.nchunks - 1;
     if (*last) a.cell_counters[it.cell] = 0;   // ready for the next call
-    __threadfence();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
   }
   __syncthreads();
   if (!*last) return false;
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
   // Each thread sums MV units at a time with MC chunks' loads in flight: the sums are on
   // the critical path of every split cell and each round is a memory latency.  (A thread
   // reads and then writes only its own units of G.)
