@@ -1568,7 +1568,6 @@ static void build_adj_items(enufft_plan_t p, int64_t c0, int64_t c1, int slots, 
 // plan is made, before any reconstruction).
 void adj_reset(enufft_plan_t p) {
   dev_release(p, &p->adj.d_items, std::max<size_t>(16, p->adj.items.size() * sizeof(AdjItem)));
-  dev_release(p, &p->adj.d_cols, std::max<size_t>(16, p->adj.cols_bytes));
   p->adj = AdjSched{};
   dev_release(p, &p->d_adj1_items, std::max<size_t>(16, p->adj1_items.size() * sizeof(AdjItem)));
   p->adj1_items.clear();
@@ -1579,6 +1578,7 @@ static enufft_status adj_alloc(enufft_plan_t p, void **d, size_t bytes, const ch
   hipError_t e = hipMalloc(d, std::max<size_t>(16, bytes));
   if (e != hipSuccess) {
     *d = nullptr;
+    (void)hipGetLastError();   // (not left for the check of a later launch)
     p->last_error = std::string(what) + " allocation failed";
     return ENUFFT_ENOMEM;
   }
@@ -1617,6 +1617,25 @@ static const void *band_fn(enufft_plan_t p, bool recon) {
 // batches run in groups of cells, one pair of launches each.
 constexpr size_t ADJ_COLS_CAP = (size_t)512 << 20;
 
+static size_t cols_per_cell(enufft_plan_t p, int nset) {
+  return (size_t)nset * p->geom.n2 * (p->geom.K1 + 1) * 2 * p->elem;
+}
+
+// The buffer of the column spectra, one for the gradients and the reconstruction (both
+// run on the plan's stream and share its work counters).  Where the device or
+// ENUFFT_ALLOC_CAP_MB leaves less room the groups get smaller, down to one cell.
+static enufft_status cols_prepare(enufft_plan_t p) {
+  if (p->d_adj_cols) return ENUFFT_OK;
+  const size_t per_cell = cols_per_cell(p, 2);
+  const int64_t room = std::min<int64_t>((int64_t)ADJ_COLS_CAP, workspace_room(p));
+  int64_t group = std::max<int64_t>(1, std::min<int64_t>(p->n_cells, room / (int64_t)per_cell));
+  for (;; group = (group + 1) / 2) {
+    const enufft_status st = adj_alloc(p, &p->d_adj_cols, per_cell * (size_t)group, "adjoint column spectra");
+    if (st == ENUFFT_OK) p->adj_cols_bytes = per_cell * (size_t)group;
+    if (st == ENUFFT_OK || group == 1) return st;
+  }
+}
+
 // Set up a banded schedule on first use (the gradients' or the reconstruction's).
 static enufft_status band_prepare(enufft_plan_t p, AdjSched *s, bool recon) {
   if (s->ready) return ENUFFT_OK;
@@ -1646,8 +1665,9 @@ static enufft_status band_prepare(enufft_plan_t p, AdjSched *s, bool recon) {
     p->last_error = "adjoint kernel cannot be resident";
     return ENUFFT_EDEVICE;
   }
-  const size_t per_cell = own ? 0 : (size_t)(recon ? 1 : 2) * p->geom.n2 * (p->geom.K1 + 1) * 2 * p->elem;
-  const int64_t fit = own ? p->n_cells : (int64_t)(ADJ_COLS_CAP / per_cell);
+  enufft_status st = own ? ENUFFT_OK : cols_prepare(p);
+  if (st != ENUFFT_OK) return st;
+  const int64_t fit = own ? p->n_cells : (int64_t)(p->adj_cols_bytes / cols_per_cell(p, recon ? 1 : 2));
   const int64_t group = std::max<int64_t>(1, std::min<int64_t>(p->n_cells, fit));
   for (int64_t c = 0; c < p->n_cells; c += group) {
     n.cell0.push_back(c);
@@ -1658,11 +1678,7 @@ static enufft_status band_prepare(enufft_plan_t p, AdjSched *s, bool recon) {
   n.cell0.push_back(p->n_cells);
   n.first.push_back((int64_t)n.items.size());
   n.slots = slots;
-  enufft_status st = adj_upload(p, &n.d_items, n.items.data(), n.items.size() * sizeof(AdjItem), "adjoint item");
-  if (st == ENUFFT_OK) {
-    n.cols_bytes = per_cell * (size_t)group;
-    st = adj_alloc(p, &n.d_cols, n.cols_bytes, "adjoint column spectra");
-  }
+  st = adj_upload(p, &n.d_items, n.items.data(), n.items.size() * sizeof(AdjItem), "adjoint item");
   if (st != ENUFFT_OK) return st;
   n.ready = true;
   *s = n;
@@ -1700,8 +1716,8 @@ enufft_status geometry_supported(enufft_plan_t p) {
 
 // Lazily set up the adjoint schedule on first use.
 enufft_status adj_prepare(enufft_plan_t p) {
+  if (p->adj1 ? p->d_adj1_items != nullptr : p->adj.ready) return ENUFFT_OK;
   if (!p->adj1) return band_prepare(p, &p->adj, false);
-  if (p->d_adj1_items) return ENUFFT_OK;
   // single-grid adjoint: one item per cell (or chunk of a large cell), no bands;
   // 512 threads, so two workgroups fit a CU with the compact layout
   if (const char *ev = std::getenv("ENUFFT_ADJ1_THREADS")) p->adj1_threads = std::atoi(ev) == 1024 ? 1024 : 512;
@@ -1711,6 +1727,7 @@ enufft_status adj_prepare(enufft_plan_t p) {
     p->last_error = "single-grid adjoint kernel cannot be resident";
     return ENUFFT_EDEVICE;
   }
+  p->adj1_items.clear();
   build_adj_items(p, 0, p->n_cells, slots, 1, 16384, p->adj1_items);
   p->adj1_blocks = (int)std::min<int64_t>(slots, std::max<int64_t>(1, (int64_t)p->adj1_items.size()));
   void *d = nullptr;
@@ -1723,8 +1740,9 @@ enufft_status adj_prepare(enufft_plan_t p) {
 // The reconstruction's schedule, with the items of each cell, ascending (a cell's
 // item partials are summed in this fixed order).
 static enufft_status rec_prepare(enufft_plan_t p) {
+  if (p->d_rec_part) return ENUFFT_OK;
   enufft_status st = band_prepare(p, &p->rec, true);
-  if (st != ENUFFT_OK || p->d_rec_part) return st;
+  if (st != ENUFFT_OK) return st;
   const std::vector<AdjItem> &items = p->rec.items;
   std::vector<int64_t> coff(p->n_cells + 1, 0);
   for (const AdjItem &it : items) ++coff[it.cell + 1];
@@ -1734,8 +1752,9 @@ static enufft_status rec_prepare(enufft_plan_t p) {
     std::vector<int64_t> pos(coff.begin(), coff.end() - 1);
     for (size_t i = 0; i < items.size(); ++i) citems[pos[items[i].cell]++] = (int32_t)i;
   }
-  st = adj_upload(p, &p->d_cell_items, citems.data(), citems.size() * sizeof(int32_t), "cell item list");
-  if (st == ENUFFT_OK)
+  if (!p->d_cell_items)
+    st = adj_upload(p, &p->d_cell_items, citems.data(), citems.size() * sizeof(int32_t), "cell item list");
+  if (st == ENUFFT_OK && !p->d_cell_item_off)
     st = adj_upload(p, &p->d_cell_item_off, coff.data(), coff.size() * sizeof(int64_t), "cell item offsets");
   if (st == ENUFFT_OK) st = cell_offsets(p);
   if (st == ENUFFT_OK)
@@ -1779,7 +1798,7 @@ static hipError_t launch_band(enufft_plan_t p, AdjArgs<T> a, const AdjSched &s) 
   const size_t lds_cols = ((size_t)a.g.n2 * (2 * cg + 2) + 2 * (size_t)a.g.n2) * sizeof(T);
   a.bands = s.bands;
   a.band_rows = s.band_rows;
-  a.cols = (T *)s.d_cols;
+  a.cols = (T *)p->d_adj_cols;
   double *part = a.rec_part;
   for (size_t q = 0; q + 1 < s.cell0.size(); ++q) {
     a.items = (const AdjItem *)s.d_items + s.first[q];

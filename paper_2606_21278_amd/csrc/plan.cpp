@@ -338,6 +338,12 @@ namespace enufft {
 
 enufft_status autotune(enufft_plan_t p);
 
+// Bytes of workspace the plan may still take under ENUFFT_ALLOC_CAP_MB.
+int64_t workspace_room(enufft_plan_t p) {
+  const int64_t cap = alloc_cap_bytes();
+  return cap < 0 ? INT64_MAX : std::max<int64_t>(0, cap - p->workspace_bytes);
+}
+
 // Free one workspace allocation made by dev_alloc (no-op for NULL).
 void dev_release(enufft_plan_t p, void **ptr, size_t bytes) {
   if (!*ptr) return;
@@ -365,10 +371,10 @@ constexpr int64_t kPercellChunkMin = 4096;
 // its last one.  64 cells of 2.1e6 points: 160 chunks of at most 16,384 to 248, the
 // forward kernel 292 to 233 us; one cell of 2,000 points: one chunk to four, 37 us to 23.
 // A smaller chunk is taken only while the partial grids stay within the allocation-free
-// entry's scratch.  FP32 plans keep the larger chunks: their partial grids are rounded to
+// entry's scratch, and under a workspace cap not at all.  FP32 plans keep the larger chunks: their partial grids are rounded to
 // FP32, so a finer split would change the results.
 static int64_t f64_chunk(enufft_plan_t p, int slots, int64_t T) {
-  if (p->n_cells > 2 * (int64_t)slots || slots < 1) return T;
+  if (p->n_cells > 2 * (int64_t)slots || slots < 1 || workspace_room(p) != INT64_MAX) return T;
   const int64_t nn = (int64_t)p->n1 * p->n2;
   const int64_t fix = 800 * nn / 16384, part = 300 * nn / 16384, sum = std::max<int64_t>(10, 40 * nn / 16384);
   const size_t room = kNoallocScratch / 2 / ((size_t)nn * p->elem);

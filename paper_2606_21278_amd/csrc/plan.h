@@ -29,10 +29,10 @@ struct UnitTable {                 // EMS units for one (use_pairs, exclude_dc) 
 struct AdjSched {
   bool ready = false;
   int bands = 1, band_rows = 0, slots = 0;
-  size_t lds = 0, cols_bytes = 0;
+  size_t lds = 0;
   std::vector<AdjItem> items;
   std::vector<int64_t> cell0, first;   // per group: its first cell and item (+ sentinels)
-  void *d_items = nullptr, *d_cols = nullptr;
+  void *d_items = nullptr;
 };
 
 }  // namespace enufft
@@ -86,6 +86,8 @@ struct enufft_plan_s {
 
   // banded schedules of the adjoint and of the reconstruction
   enufft::AdjSched adj, rec;
+  void *d_adj_cols = nullptr;        // column spectra of a group of cells, used by both
+  size_t adj_cols_bytes = 0;
   void *d_rec_part = nullptr;        // [items][3] doubles: per-item reconstruction sums
   void *d_cell_items = nullptr;      // int32 item indices grouped by cell (ascending)
   void *d_cell_item_off = nullptr;   // int64 [n_cells + 1] offsets into d_cell_items
@@ -162,6 +164,7 @@ FwdArgs<T> make_fwd_args(enufft_plan_t p, const void *x, const void *y, const vo
 enufft_status check_plan(enufft_plan_t p, const char *fn);
 // Workspace helpers shared by the translation units (defined with the plan).
 void dev_release(enufft_plan_t p, void **ptr, size_t bytes);
+int64_t workspace_room(enufft_plan_t p);
 enufft_status install_fwd_schedule(enufft_plan_t p);
 enufft_status set_fwd_threads(enufft_plan_t p, int threads, size_t lds_limit);
 void adj_reset(enufft_plan_t p);
