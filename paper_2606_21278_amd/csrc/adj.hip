@@ -1573,6 +1573,27 @@ void adj_reset(enufft_plan_t p) {
   p->adj1_items.clear();
 }
 
+// While the caller's stream is being captured, allocations and uploads of a first call
+// would be refused (a capture records launches): they run outside it, the uploads on a
+// stream of their own (the default stream would join the capture).
+struct OutsideCapture {
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  OutsideCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+  ~OutsideCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+};
+
+static hipError_t outside_copy(enufft_plan_t p, void *d, const void *src, size_t bytes) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(p->stream, &st) != hipSuccess) (void)hipGetLastError();
+  if (st == hipStreamCaptureStatusNone) return hipMemcpy(d, src, bytes, hipMemcpyHostToDevice);
+  hipStream_t s = nullptr;
+  hipError_t e = hipStreamCreateWithFlags(&s, hipStreamNonBlocking);
+  if (e == hipSuccess) e = hipMemcpyAsync(d, src, bytes, hipMemcpyHostToDevice, s);
+  if (e == hipSuccess) e = hipStreamSynchronize(s);
+  if (s) (void)hipStreamDestroy(s);
+  return e;
+}
+
 // Device allocation recorded in the plan's workspace (released with the plan).
 static enufft_status adj_alloc(enufft_plan_t p, void **d, size_t bytes, const char *what) {
   hipError_t e = hipMalloc(d, std::max<size_t>(16, bytes));
@@ -1590,7 +1611,7 @@ static enufft_status adj_alloc(enufft_plan_t p, void **d, size_t bytes, const ch
 static enufft_status adj_upload(enufft_plan_t p, void **d, const void *src, size_t bytes, const char *what) {
   enufft_status st = adj_alloc(p, d, bytes, what);
   if (st != ENUFFT_OK || bytes == 0) return st;
-  const hipError_t e = hipMemcpy(*d, src, bytes, hipMemcpyHostToDevice);
+  const hipError_t e = outside_copy(p, *d, src, bytes);
   if (e != hipSuccess) {
     p->last_error = std::string(what) + " upload: " + hipGetErrorString(e);
     p->faulted = true;
@@ -1689,6 +1710,7 @@ static enufft_status band_prepare(enufft_plan_t p, AdjSched *s, bool recon) {
 // on first use.
 enufft_status cell_offsets(enufft_plan_t p) {
   if (p->d_cell_off) return ENUFFT_OK;
+  const OutsideCapture outside;
   return adj_upload(p, &p->d_cell_off, p->offsets.data(), p->offsets.size() * sizeof(int64_t), "cell offsets");
 }
 
@@ -1717,6 +1739,7 @@ enufft_status geometry_supported(enufft_plan_t p) {
 // Lazily set up the adjoint schedule on first use.
 enufft_status adj_prepare(enufft_plan_t p) {
   if (p->adj1 ? p->d_adj1_items != nullptr : p->adj.ready) return ENUFFT_OK;
+  const OutsideCapture outside;
   if (!p->adj1) return band_prepare(p, &p->adj, false);
   // single-grid adjoint: one item per cell (or chunk of a large cell), no bands;
   // 512 threads, so two workgroups fit a CU with the compact layout
@@ -1741,6 +1764,7 @@ enufft_status adj_prepare(enufft_plan_t p) {
 // item partials are summed in this fixed order).
 static enufft_status rec_prepare(enufft_plan_t p) {
   if (p->d_rec_part) return ENUFFT_OK;
+  const OutsideCapture outside;
   enufft_status st = band_prepare(p, &p->rec, true);
   if (st != ENUFFT_OK) return st;
   const std::vector<AdjItem> &items = p->rec.items;

@@ -1,7 +1,7 @@
 """Workspace of the banded adjoint and of the reconstruction: the column spectra are held
 for a group of cells at a time, the groups shrink with the room ENUFFT_ALLOC_CAP_MB leaves
 (down to one cell) instead of refusing the call, and one buffer serves both.  Results do
-not depend on the grouping."""
+not depend on the grouping.  A first call may also stand inside a stream capture."""
 import numpy as np
 import pytest
 import torch
@@ -72,3 +72,27 @@ def test_chunks_under_a_cap(monkeypatch):
     capped = make_plan(gb).info()
     assert fine["n_items_fwd"] > coarse["n_items_fwd"] == capped["n_items_fwd"]
     assert fine["workspace_bytes"] > coarse["workspace_bytes"] == capped["workspace_bytes"]
+
+
+@pytest.mark.parametrize("prec", ["f64", "f32"])
+@pytest.mark.parametrize("warm", ["adj", "rec", None])
+def test_first_call_inside_a_capture(prec, warm):
+    gb = gpu_batch(_batch(prec))
+    ref = _run(gb, make_plan(gb))
+    plan = make_plan(gb)
+    adj, rec = _calls(gb, plan)
+    if warm:
+        adj() if warm == "adj" else rec()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        out = (adj() if warm != "adj" else []) + (rec() if warm != "rec" else [])
+    want = (ref[:3] if warm != "adj" else []) + (ref[3:] if warm != "rec" else [])
+    for _ in range(3):
+        for t in out:
+            if t is not None:
+                t.fill_(-1)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert _same(out, want)
+        assert _same(_run(gb, plan), ref)   # eager calls between the replays
