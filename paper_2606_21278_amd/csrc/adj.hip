@@ -486,12 +486,15 @@ __device__ __forceinline__ void gather_point(const AdjArgs<T> &a, const T *G, co
     }
   };
   if constexpr (POLY && sizeof(T) == 8) {
-    es_taps_poly64<W>(tap_u64(fx, double(W) * 0.5), a.es64, kx);
+    es_taps64<W>(tap_u64(fx, double(W) * 0.5), a.es64, kx);
     const double uyv = tap_u64(fy, double(W) * 0.5), sy2 = uyv * uyv;
     // two rows at a time, so the loads of all W rows are not held in registers together
+    double ta, tb;
+    tap_pair64<W>(a.es64, 0, uyv, sy2, ta, tb);
+    row(0, ta);
+    row(W - 1, tb);
 #pragma unroll 1
-    for (int d = 0; d < W / 2; ++d) {
-      double ta, tb;
+    for (int d = 1; d < W / 2; ++d) {
       poly64_pair_eval(poly64_pair(a.es64, d), uyv, sy2, ta, tb);
       row(d, ta);
       row(W - 1 - d, tb);

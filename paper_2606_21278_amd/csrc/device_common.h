@@ -37,17 +37,28 @@ struct EsPoly {
   float c[(ES_MAXW / 2) * (ES_DEG + 1)];   // taps 0 .. W/2 - 1, tap-major, ascending powers of u = 2 v - 1
 };
 
-// The same per-tap form in FP64 for FP64 plans: degree 13 reproduces the taps to
-// about 5e-13 at W = 12 and 6e-15 at W = 14 (the outer tap's square-root branch
-// point at the edge of the support limits the fit up to W = 12, not the degree).
+// The same per-tap form in FP64 for FP64 plans.  Degree 13 gives the inner taps to a
+// rounding error (1e-15 from W = 10, 4e-15 at W = 8, 3e-14 at W = 6).  The outermost pair
+// it does not: psi has a square-root branch point at the edge of its support, and the
+// deviation there is about half of psi's own jump (3.8e-7 at W = 6, 4.4e-9 at W = 8,
+// 4.8e-11 at W = 10, 5.2e-13 at W = 12, 6e-15 at W = 14), half a percent of the accuracy the width
+// is chosen for.  From W = 10, and in large cells, every tap is taken so (on = 1): against
+// 64-bit sums the results' errors are those of psi itself to two digits and more (1,500
+// cells of 1,500 points, W = 10: 1.5e-9 both; W = 12, 64 cells: 1.8e-11 both), and
+// splitting the pair there made the rows of lanes 5 to 15 % slower.  Up to W = 8 the
+// outputs would move by up to 1e-8; there small cells split the pair at the branch point
+// (on = 2; 2 to 7 % of a call): with s = sqrt(1 - z^2), psi = e^-beta (cosh(beta s) +
+// sinh(beta s)), whose first part and the second over sqrt(v), v the distance from the
+// edge, are entire functions of v: E(u) + sqrt(v) Q(u), each of degree 13 (2e-14 at
+// W = 6, 1e-15 at W = 8).
 // The table is in device memory, read through scalar loads (the same address for
 // every lane): by value in the kernel arguments, a pair chosen in a loop made the
 // compiler copy the whole argument block to every lane's scratch.
 constexpr int ES64_DEG = 13;
 constexpr int ES64_MAXW = 16;
 struct EsPoly64 {
-  int on;
-  const double *c;   // (W / 2)(ES64_DEG + 1) coefficients, as EsPoly
+  int on;            // 0: psi itself, 1: polynomials, 2: the outermost pair split at the branch point
+  const double *c;   // (W / 2)(ES64_DEG + 1) coefficients, as EsPoly; on = 2: pair 0 holds E, and Q follows
 };
 typedef const double __attribute__((address_space(4))) *ScalarTable;
 
@@ -371,6 +382,42 @@ __device__ __forceinline__ void es_taps_poly64(double u, const EsPoly64 &cf, dou
   const double s = u * u;
 #pragma unroll
   for (int d = 0; d < W / 2; ++d) poly64_pair_eval(poly64_pair(cf, d), u, s, out[d], out[W - 1 - d]);
+}
+
+// Square root of v in [0, 1] to about a rounding error (the hardware's reciprocal square
+// root, one Newton step).
+__device__ __forceinline__ double sqrt_unit(double v) {
+  const double w = fmax(v, 1e-300), y = __builtin_amdgcn_rsq(w), s = w * y;
+  return fma(0.5 * y, fma(-s, s, w), s);
+}
+
+// The outermost pair, taps 0 and W - 1, of a small-cell plan up to W = 8.
+template <int W>
+__device__ __forceinline__ void outer_taps64(const EsPoly64 &cf, double u, double &t0, double &t1) {
+  const ScalarTable ce = poly64_pair(cf, 0);
+  const double s = u * u;
+  poly64_pair_eval(ce, u, s, t0, t1);
+  if (cf.on == 2) {
+    double q0, q1;
+    poly64_pair_eval(ce + (W / 2) * (ES64_DEG + 1), u, s, q0, q1);
+    t0 = fma(sqrt_unit(fma(0.5, u, 0.5)), q0, t0);
+    t1 = fma(sqrt_unit(fma(-0.5, u, 0.5)), q1, t1);
+  }
+}
+
+// Mirror pair d of a small-cell plan (d known at compile time, or not 0).
+template <int W>
+__device__ __forceinline__ void tap_pair64(const EsPoly64 &cf, int d, double u, double s, double &t0, double &t1) {
+  if (W <= 8 && d == 0) outer_taps64<W>(cf, u, t0, t1);
+  else poly64_pair_eval(poly64_pair(cf, d), u, s, t0, t1);
+}
+
+// All W taps of one axis in a small-cell plan.
+template <int W>
+__device__ __forceinline__ void es_taps64(double u, const EsPoly64 &cf, double (&out)[W]) {
+  const double s = u * u;
+#pragma unroll
+  for (int d = 0; d < W / 2; ++d) tap_pair64<W>(cf, d, u, s, out[d], out[W - 1 - d]);
 }
 
 // Rows of sixteen lanes with one point each (FP64, W > 8): lane d of a row holds tap d of

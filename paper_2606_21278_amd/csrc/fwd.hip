@@ -55,13 +55,13 @@ __device__ __forceinline__ void spread_point(const FwdArgs<T> &a, A *grid, T c, 
     // FP64: the x taps, then the rows in mirror pairs, whose y taps come from one
     // polynomial pair (its coefficients read where they are used)
     T kx[W];
-    es_taps_poly64<W>(tap_u64(fx, double(W) * 0.5), a.es64, kx);
+    es_taps64<W>(tap_u64(fx, double(W) * 0.5), a.es64, kx);
     const T u = tap_u64(fy, double(W) * 0.5), s = u * u;
     const int c0 = fx.i0, r0 = fy.i0 & (g.n2 - 1);
 #pragma unroll
     for (int d = 0; d < W / 2; ++d) {
       T ta, tb;
-      poly64_pair_eval(poly64_pair(a.es64, d), u, s, ta, tb);
+      tap_pair64<W>(a.es64, d, u, s, ta, tb);
       ta *= c;
       tb *= c;
       A *pa = grid + (r0 + d) * pitch, *pb = grid + (r0 + W - 1 - d) * pitch;

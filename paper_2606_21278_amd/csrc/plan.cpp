@@ -217,11 +217,14 @@ double kernel_deriv_host(double z, double shape) {
 // Per-tap polynomials in u = 2 v - 1, v = i0 - t + W/2 in [0, 1) (tap d sits at
 // z = (v + d - W/2) 2 / W): Chebyshev interpolation of f(d, z) at deg + 1 nodes,
 // converted to monomial coefficients (ascending).  Returns the largest deviation on
-// a fine sample.
+// a fine sample; outer: that of the outermost pair alone, the result then that of the
+// others.  (Both ends of the interval are sampled, where the deviation of the outermost
+// pair is largest; 2,001 points instead of 401 find at most 0.3 % more.)
 template <typename F>
-double fit_tap_poly(int W, int deg, const F &f, std::vector<double> &coef) {
+double fit_tap_poly(int W, int deg, const F &f, std::vector<double> &coef, double *outer = nullptr) {
   coef.assign((size_t)W * (deg + 1), 0.0);
   double maxerr = 0.0;
+  if (outer) *outer = 0.0;
   const int n = deg + 1;
   std::vector<double> cheb(n), yn(n), un(n), ct((size_t)n * n);
   for (int j = 0; j < n; ++j)
@@ -253,15 +256,44 @@ double fit_tap_poly(int W, int deg, const F &f, std::vector<double> &coef) {
       const double v = i / 400.0, u = 2.0 * v - 1.0;
       double acc = coef[(size_t)d * n + deg];
       for (int k = deg - 1; k >= 0; --k) acc = acc * u + coef[(size_t)d * n + k];
-      maxerr = std::max(maxerr, std::fabs(acc - f(d, (v + d - 0.5 * W) * 2.0 / W)));
+      double &worst = outer && d == 0 ? *outer : maxerr;
+      worst = std::max(worst, std::fabs(acc - f(d, (v + d - 0.5 * W) * 2.0 / W)));
     }
   }
   return maxerr;
 }
 
+// The ES kernel's outermost pair in FP64, split at its branch point: tap 0 sits at
+// z = -1 + 2 v / W, psi = e^-beta (cosh(beta s) + sinh(beta s)) with s = sqrt(1 - z^2); E is
+// the first part, Q the second over sqrt(v).  coef: E's and Q's coefficients.  Returns the
+// largest deviation of E + sqrt(v) Q from psi.
+double fit_outer_pair(int W, double beta, int deg, std::vector<double> &coef) {
+  // tap 0 of a kernel of one tap is a function of v = (z + 1) / 2
+  std::vector<double> e, q;
+  auto arg = [&](double v) { return beta * std::sqrt(4.0 * v / W * (1.0 - v / W)); };
+  fit_tap_poly(1, deg, [&](int, double z) { return std::exp(-beta) * std::cosh(arg(0.5 * (z + 1.0))); }, e);
+  fit_tap_poly(1, deg, [&](int, double z) {
+    const double v = std::max(0.5 * (z + 1.0), 1e-12);
+    return std::exp(-beta) * std::sinh(arg(v)) / std::sqrt(v);
+  }, q);
+  double maxerr = 0.0;
+  for (int i = 0; i <= 400; ++i) {
+    const double v = i / 400.0, u = 2.0 * v - 1.0;
+    double ve = e[deg], vq = q[deg];
+    for (int k = deg - 1; k >= 0; --k) {
+      ve = ve * u + e[k];
+      vq = vq * u + q[k];
+    }
+    maxerr = std::max(maxerr, std::fabs(ve + std::sqrt(v) * vq - es_host(2.0 * v / W - 1.0, beta)));
+  }
+  coef = e;
+  coef.insert(coef.end(), q.begin(), q.end());
+  return maxerr;
+}
+
 // The kernel's taps as polynomials (the forward and both adjoints).
-double fit_es_poly(int W, double beta, int deg, std::vector<double> &coef) {
-  return fit_tap_poly(W, deg, [&](int, double z) { return kernel_host(z, beta); }, coef);
+double fit_es_poly(int W, double beta, int deg, std::vector<double> &coef, double *outer = nullptr) {
+  return fit_tap_poly(W, deg, [&](int, double z) { return kernel_host(z, beta); }, coef, outer);
 }
 
 // Largest deviation of the fitted taps' derivatives with respect to the fine coordinate t,
@@ -280,6 +312,9 @@ double tap_deriv_error(int W, double beta, int deg, const std::vector<double> &c
   }
   return maxerr;
 }
+
+// Largest deviation from psi of the FP64 taps of a small-cell plan up to W = 8.
+constexpr double ES64_FIT_EXACT = 1e-13;
 
 int64_t alloc_cap_bytes() {
   const char *s = std::getenv("ENUFFT_ALLOC_CAP_MB");
@@ -642,17 +677,32 @@ enufft_status enufft_plan(enufft_plan_t *out, int64_t n_cells, const int64_t *ce
   }
 
   // FP64 plans: the same per-tap form in FP64 (even widths), kept when its fit is at
-  // least ten times below the requested accuracy
+  // least ten times below the requested accuracy; in small cells up to W = 8, where the
+  // outermost pair's deviation would show in the outputs, only with that pair exact to a
+  // rounding error (the reasons and figures stand at EsPoly64)
   std::vector<double> es64;
   if (p->prec == ENUFFT_F64 && W % 2 == 0 && W <= enufft::ES64_MAXW) {
     const char *ev = std::getenv("ENUFFT_POLY64");
     if (!(ev && std::atoi(ev) == 0)) {
       std::vector<double> cf;
-      const double err = fit_es_poly(W, beta, enufft::ES64_DEG, cf);
-      if (err <= 0.1 * opts->eps) {
+      double outer = 0.0;
+      const double inner = fit_es_poly(W, beta, enufft::ES64_DEG, cf, &outer);
+      double err = std::max(inner, outer);
+      const size_t row = enufft::ES64_DEG + 1;
+      cf.resize((size_t)(W / 2) * row);
+      const bool exact = !big && W <= 8;
+      int on = err <= (exact ? ES64_FIT_EXACT : 0.1 * opts->eps);
+      if (exact && !on && !kb) {
+        std::vector<double> eq;
+        err = std::max(inner, fit_outer_pair(W, beta, enufft::ES64_DEG, eq));
+        std::copy(eq.begin(), eq.begin() + row, cf.begin());
+        cf.insert(cf.end(), eq.begin() + row, eq.end());
+        on = err <= ES64_FIT_EXACT ? 2 : 0;
+      }
+      if (on) {
         p->es_poly_err = err;
-        p->es64.on = 1;
-        es64.assign(cf.begin(), cf.begin() + (size_t)(W / 2) * (enufft::ES64_DEG + 1));
+        p->es64.on = on;
+        es64 = cf;
       }
     }
   }
