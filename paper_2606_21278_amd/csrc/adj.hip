@@ -281,14 +281,17 @@ struct RowSpecAcc {
 
 // First-step accessor of the column transforms from global memory: as
 // ColSpecAcc, reading the cell's coefficients, keep bytes and deconvolution
-// factors in place.  Loads are unconditional (bins outside the box read mode 0
-// and are masked), so those of one transform are in flight together.
+// factors in place.  A bin's loads are issued together (without a keep mask the
+// coefficients' bytes are read in its place, so no test of its presence parts them); with
+// that test between them a bin cost three latencies and 4,000 cells of FP32 columns
+// 325 us.  (All bins' loads at once, with factors for the masks, need 184 registers in
+// FP32 and 266 in FP64: 2 us less for 60 cells, 100 more for 4,000.)
 template <typename T>
 struct ColSpecGlobal {
   const typename vec2<T>::type *sf;
   const T *dx, *dy;
   const uint8_t *kp;
-  T two_lam;
+  T two_lam, dropped;   // factors of kept and of other modes (both 1 without a mask)
   T *col;
   int cpitch, kx, n2, K2, N1, lo1, lo2, hi1, hi2;
   bool yderiv;
@@ -299,11 +302,7 @@ struct ColSpecGlobal {
     const bool q = in && -kx >= lo1 && -ky >= lo2 && -ky <= hi2;
     const int mp = p ? (ky - lo2) * N1 + (kx - lo1) : 0, mq = q ? (-ky - lo2) * N1 + (-kx - lo1) : 0;
     const auto vp = sf[mp], vq = sf[mq];
-    T sp = T(1), sq = T(1);
-    if (kp) {
-      sp = kp[mp] ? two_lam : T(0);
-      sq = kp[mq] ? two_lam : T(0);
-    }
+    const T sp = kp[mp] ? two_lam : dropped, sq = kp[mq] ? two_lam : dropped;
     const T s = T(0.5) * (dx[kx] * dy[in ? (ky < 0 ? -ky : ky) : 0]);
     T hr = p ? sp * vp.x : T(0), hi = p ? sp * vp.y : T(0);
     hr += q ? sq * vq.x : T(0);
@@ -357,9 +356,10 @@ __global__ __launch_bounds__(ADJ_COLS_THREADS) void adj_cols_kernel(AdjArgs<T> a
   acc.sf = reinterpret_cast<const typename vec2<T>::type *>(a.fbar) + (int64_t)cell * g.N1 * g.N2;
   acc.dx = a.decon_x;
   acc.dy = a.decon_y;
-  acc.kp = a.keep ? a.keep + (int64_t)cell * g.N1 * g.N2 : nullptr;
+  acc.kp = a.keep ? a.keep + (int64_t)cell * g.N1 * g.N2 : reinterpret_cast<const uint8_t *>(acc.sf);
   // the reconstruction's coefficients are kept or dropped, not weighted
-  acc.two_lam = a.rec_part ? T(1) : T(2.0 * (a.lam ? a.lam[cell] : 1.0));
+  acc.two_lam = a.rec_part || !a.keep ? T(1) : T(2.0 * (a.lam ? a.lam[cell] : 1.0));
+  acc.dropped = a.keep ? T(0) : T(1);
   acc.cpitch = 2 * cg + 2;
   acc.n2 = n2; acc.K2 = g.K2; acc.N1 = g.N1; acc.lo1 = g.lo1; acc.lo2 = g.lo2;
   acc.hi1 = g.lo1 + g.N1 - 1; acc.hi2 = g.lo2 + g.N2 - 1;
@@ -621,14 +621,19 @@ __device__ __forceinline__ void gather_rows(const double *G, const double *Gy, i
 // next point loaded while the current one is gathered.  Otherwise every y of the
 // item is read and the points of the band are queued per wave and gathered 64 at
 // a time: served where they stand, only one lane in `bands` would be active for
-// points in no spatial order, at the cost of a whole wave's gather each time.
+// points in no spatial order, at the cost of a whole wave's gather each time.  Up to
+// W = 8 a wave whose points all lie in the band serves them where they stand, as raster
+// points mostly do.  The waves take the item's blocks of 64 points in turn: with blocks of
+// 256 to a wave an item of 600 points had kept three of the eight waves busy.  Both
+// together, FP32, W = 8, raster points: 4,000 cells of 600 1,010 to 927 us, 60 of 28,000
+// 106.5 to 103.3; FP64, W = 10, 1,500 cells of 600 936 to 620 us, of which the column
+// launch's loads (ColSpecGlobal) are part.
 template <typename T, int W, int NT, bool POLY, bool RECON>
 __device__ __forceinline__ void gather_item(const AdjArgs<T> &a, const T *G, const T *Gy, int apitch, int *queue,
                                             int band_lo, int64_t begin, int64_t end, T cx, T cy, T R,
                                             double (&acc)[3]) {
   const T pr = R > T(0) ? T(M_PI) / R : T(0);
   const T halfw = T(W) / T(2);
-  constexpr int NWV = NT / 64;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int mask2 = a.g.n2 - 1;
   if (begin >= end) return;
@@ -662,8 +667,8 @@ __device__ __forceinline__ void gather_item(const AdjArgs<T> &a, const T *G, con
                                         acc);
       }
     };
-    const int64_t stride = (int64_t)NWV * 64;
-    int64_t i = begin + (int64_t)wave * 64 + lane;
+    constexpr int64_t stride = NT;
+    int64_t i = begin + threadIdx.x;
     Pt b0, b1;
     load(b0, i);
     for (; i - lane < end; i += 2 * stride) {
@@ -674,15 +679,15 @@ __device__ __forceinline__ void gather_item(const AdjArgs<T> &a, const T *G, con
     }
     return;
   }
-  constexpr int U = 4, BLK = 64 * U;
+  constexpr int U = 4;
   int *wq = queue + wave * ADJ_QCAP;
-  auto drain = [&](int n) {
-    if constexpr (kRows) {   // neighbours of the queue in different rows, so a short one fills all
-      const int k = (lane & 15) * 4 + (lane >> 4);
-      const int64_t j = begin + wq[min(k, n - 1)];
-      rows(k < n, j, a.x[j], a.y[j], a.h[j], a.w[j], band_lo);
-    } else if (lane < n) {
-      const int64_t j = begin + wq[lane];
+  // the queue's entry of a lane (rows of lanes: neighbours of the queue in different rows,
+  // so a short one fills all)
+  const int slot = kRows ? (lane & 15) * 4 + (lane >> 4) : lane;
+  auto serve = [&](bool on, int64_t j) {
+    if constexpr (kRows) {
+      rows(on, j, a.x[j], a.y[j], a.h[j], a.w[j], band_lo);
+    } else if (on) {
       const T xj = a.x[j], yj = a.y[j], hj = a.h[j], wj = a.w[j];
       const FineCoord<T> fy = fine_coord<T>(yj, a.s2_hi, a.s2_lo, halfw);
       gather_point<T, W, POLY, RECON>(a, G, Gy, apitch, (fy.i0 & mask2) - band_lo, fy, j, xj, yj, hj, wj, cx, cy, R,
@@ -698,44 +703,43 @@ __device__ __forceinline__ void gather_item(const AdjArgs<T> &a, const T *G, con
   T yb[U];
   auto load = [&](int64_t p) {
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int64_t i = p + u * 64 + lane;
-      yb[u] = a.y[i < end ? i : end - 1];
-    }
+    for (int u = 0; u < U; ++u) yb[u] = a.y[min(p + u * NT + (int)threadIdx.x, end - 1)];
   };
-  int64_t p = begin + (int64_t)wave * BLK;
-  load(p);
-  for (; p < end; p += (int64_t)NWV * BLK) {
+  load(begin);
+  for (int64_t p = begin; p < end; p += U * NT) {
     bool in[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int r0 = (fine_coord<T>(yb[u], a.s2_hi, a.s2_lo, halfw).i0 & mask2) - band_lo;
-      in[u] = p + u * 64 + lane < end && r0 >= 0 && r0 < a.band_rows;
+      in[u] = p + u * NT + (int)threadIdx.x < end && r0 >= 0 && r0 < a.band_rows;
     }
-    load(p + (int64_t)NWV * BLK);
+    load(p + U * NT);
 #pragma unroll 1
     for (int u = 0; u < U; ++u) {
       const bool on = u == 0 ? in[0] : u == 1 ? in[1] : u == 2 ? in[2] : in[3];
       const uint64_t m = __ballot(on);
       if (m == 0) continue;
-      if (on) {
-        const int pos = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-        wq[nq + pos] = (int)(p + u * 64 + lane - begin);   // nq < 64 here, so nq + pos < ADJ_QCAP
-      }
-      nq += __popcll(m);
-      if (nq >= 64) {
+      int64_t j = p + u * NT + (int)threadIdx.x;
+      if (kRows || m != ~0ull) {
+        if (on) {
+          const int pos = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+          wq[nq + pos] = (int)(j - begin);   // nq < 64 here, so nq + pos < ADJ_QCAP
+        }
+        nq += __popcll(m);
+        if (nq < 64) continue;
         order();
-        drain(64);
         nq -= 64;
+        j = begin + wq[slot];
         const int rest = lane < nq ? wq[64 + lane] : 0;
         order();
         if (lane < nq) wq[lane] = rest;
         order();
       }
+      serve(true, j);
     }
   }
   order();
-  if (nq > 0) drain(nq);
+  if (nq > 0) serve(slot < nq, begin + wq[min(slot, nq - 1)]);
 }
 
 template <typename T, int W, int NT, bool POLY, bool RECON>
