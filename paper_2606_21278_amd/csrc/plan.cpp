@@ -400,31 +400,40 @@ constexpr int64_t kPercellChunkMin = 4096;
 
 // Chunk size of an FP64 plan whose user and tuner named none.  Below 16,384 points a
 // chunk pays as long as workgroups would idle: the sizes from T down to 512 points are
-// compared by the end of a longest-first schedule, in points of spreading time (41
-// cycles each): an item's zeroing, folding and transform are about 800 points on a 128^2
-// grid, a split cell's exchange another 300 per chunk and 40 per chunk of the cell for
-// its last one.  64 cells of 2.1e6 points: 160 chunks of at most 16,384 to 248, the
-// forward kernel 292 to 233 us; one cell of 2,000 points: one chunk to four, 37 us to 23.
+// compared by the end of a longest-first schedule.  The costs (ns, fitted to sweeps of one to
+// 600 cells of 1,500 to 60,000 points on 32^2, 64^2 and 128^2 grids at W = 6, 8, 10 and 14): a point by
+// the kernel's width; an item's zeroing, folding and transform; a split cell's exchange;
+// and for its last chunk each further round of the four grids it sums at a time.
+//   one cell of 60,000 points, 128^2, W = 10: four chunks 205 us, 15 110 us (taken), 41 151
+//   300 cells of 3,000, 32^2, W = 6: whole 62 us (taken), five chunks each 102
+//   64 cells of 2.1e6 points, 128^2, W = 12: at most 16,384 points 292 us, 233 with finer ones
 // A smaller chunk is taken only while the partial grids stay within the allocation-free
-// entry's scratch, and under a workspace cap not at all.  FP32 plans keep the larger chunks: their partial grids are rounded to
-// FP32, so a finer split would change the results.
+// entry's scratch, and under a workspace cap not at all.  FP32 plans keep the larger
+// chunks: their partial grids are rounded to FP32, so a finer split would change the results.
 static int64_t f64_chunk(enufft_plan_t p, int slots, int64_t T) {
   if (p->n_cells > 2 * (int64_t)slots || slots < 1 || workspace_room(p) != INT64_MAX) return T;
-  const int64_t nn = (int64_t)p->n1 * p->n2;
-  const int64_t fix = 800 * nn / 16384, part = 300 * nn / 16384, sum = std::max<int64_t>(10, 40 * nn / 16384);
+  static const int kPointPs[] = {4000, 6500, 10500, 11000, 12500, 14000, 16000};   // W = 4, 6 .. 16
+  const int64_t nn = (int64_t)p->n1 * p->n2, point = kPointPs[(p->W - 4) / 2];
+  const int64_t fix = 7500 + 11000 * nn / 16384, part = 4000 + 10000 * nn / 16384, round = 3000 + 6400 * nn / 16384;
   const size_t room = kNoallocScratch / 2 / ((size_t)nn * p->elem);
   int64_t best = T, best_end = -1;
   std::vector<int64_t> cost, end;
   for (int64_t t = T; t >= 512; t = t * 7 / 8) {
     cost.clear();
     size_t parts = 0;
+    int64_t sum = 0, top = 0;
     for (int64_t c = 0; c < p->n_cells; ++c) {
       const int64_t q = p->offsets[c + 1] - p->offsets[c], nch = std::max<int64_t>(1, (q + t - 1) / t);
-      for (int64_t i = 0; i < nch; ++i)
-        cost.push_back(fix + (q + nch - 1) / nch + (nch > 1 ? part : 0) + (nch > 1 && i == 0 ? sum * nch : 0));
+      const int64_t item = fix + (nch > 1 ? part : 0) + (q + nch - 1) / nch * point / 1000;
+      for (int64_t i = 0; i < nch; ++i) cost.push_back(item + (i == 0 ? (nch - 1) / 4 * round : 0));
+      sum += nch * item;
+      top = std::max(top, item + (nch - 1) / 4 * round);
       if (nch > 1) parts += (size_t)nch;
     }
     if (t < T && parts > room) break;
+    // (3 % better, or it is not taken; no schedule ends before its longest item or mean)
+    const int64_t limit = best_end < 0 ? INT64_MAX : best_end - best_end / 32;
+    if (std::max(top, sum / slots) >= limit) continue;
     std::sort(cost.begin(), cost.end(), std::greater<int64_t>());
     end.assign((size_t)slots, 0);   // min-heap of the workgroups' ends
     for (int64_t v : cost) {
@@ -433,7 +442,7 @@ static int64_t f64_chunk(enufft_plan_t p, int slots, int64_t T) {
       std::push_heap(end.begin(), end.end(), std::greater<int64_t>());
     }
     const int64_t last = *std::max_element(end.begin(), end.end());
-    if (best_end < 0 || last < best_end) {
+    if (last < limit) {
       best_end = last;
       best = t;
     }
@@ -446,6 +455,7 @@ void build_fwd_schedule(enufft_plan_t p, int slots) {
   const int64_t per = (int64_t)p->fwd_items_per_slot * std::max(1, slots);
   int64_t T = std::max<int64_t>(p->fwd_chunk_min, (Q + per - 1) / per);
   if (p->prec == ENUFFT_F64 && p->fwd_chunk_auto) T = f64_chunk(p, slots, T);
+  p->fwd_chunk = T;
   p->fwd_items.clear();
   p->fwd_items_cell.clear();
   p->fwd_cell_first.assign(p->n_cells + 1, 0);
@@ -887,7 +897,7 @@ enufft_status enufft_get_info(enufft_plan_t p, enufft_plan_info *info) {
   info->kernel_poly_err = p->es_poly_err;
   info->tuned = p->tuned;
   info->tune_cache_hit = p->tune_cache_hit;
-  info->fwd_chunk_min = p->fwd_chunk_min;
+  info->fwd_chunk_min = std::min(p->fwd_chunk_min, p->fwd_chunk);
   info->fwd_items_per_slot = p->fwd_items_per_slot;
   info->adj_items_per_slot = p->adj_items_per_slot;
   info->adj_band_mult = p->adj_band_mult;

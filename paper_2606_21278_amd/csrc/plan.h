@@ -54,6 +54,7 @@ struct enufft_plan_s {
   // launch-shape parameters (defaults, or chosen by the autotuner)
   int64_t fwd_chunk_min = 16384;   // smallest forward work item (points)
   bool fwd_chunk_auto = true;      // FP64: smaller ones where workgroups would idle
+  int64_t fwd_chunk = 16384;       // the chunk size of the present schedule
   int fwd_items_per_slot = 2;      // target forward items per resident workgroup
   int adj_items_per_slot = 2;      // same for the adjoint
   int adj_band_mult = 1;           // adjoint bands = mult x the fewest that fit LDS
