@@ -1800,7 +1800,7 @@ enufft_status type1_t(enufft_plan_t p, const T *x, const T *y, const T *h, const
         a.done_counter = p->big_work + 1;
         bool done = false;
         if constexpr (sizeof(T) == 8) {
-          if ((done = m64_use(p->W, a.es64))) e = m64_launch(p->W, a, false, tile_blocks(p, n), p->stream);
+          if ((done = m64_use(p, a.es64, n))) e = m64_launch(p->W, a, false, tile_blocks(p, n), p->stream);
         }
         if (!done) e = by_width<T, SpreadW>(p->W, a, tile_blocks(p, n), p->stream);
         // cells whose points are in fine-cell order: the run kernel (the kernel
@@ -1867,7 +1867,7 @@ enufft_status adjoint_t(enufft_plan_t p, const T *x, const T *y, const T *h, con
       a.done_counter = p->big_work + 3;
       bool done = false;
       if constexpr (sizeof(T) == 8) {
-        if ((done = m64_use(p->W, a.es64))) e = m64_launch(p->W, a, true, tile_blocks(p, n), p->stream);
+        if ((done = m64_use(p, a.es64, n))) e = m64_launch(p->W, a, true, tile_blocks(p, n), p->stream);
       }
       if (!done) e = by_width<T, GatherW>(p->W, a, tile_blocks(p, n), p->stream);
     }
@@ -1962,6 +1962,8 @@ enufft_status big_prepare(enufft_plan_t p) {
     e = p->prec == ENUFFT_F64 ? set_attrs_t<double>(g.n1, g.n2, ntiles) : set_attrs_t<float>(g.n1, g.n2, ntiles);
   if (e == hipSuccess) e = p->prec == ENUFFT_F64 ? gather_attrs<double>() : gather_attrs<float>();
   if (e == hipSuccess && p->prec == ENUFFT_F64) e = m64_attrs();
+  p->m64_per_tile = (int64_t)p->big_ntx * p->big_nty > 4 * (int64_t)p->n_cu ? M64_PER_TILE_MANY : M64_PER_TILE;
+  if (const char *ev = std::getenv("ENUFFT_M64_PER_TILE")) p->m64_per_tile = std::atof(ev);
   if (e == hipSuccess) e = hipDeviceSynchronize();
   return big_fail(p, e, "large-cell workspace");
 }

@@ -17,10 +17,11 @@
 // (taps, window, coordinates: about 600 FP64 instructions per 64 points each) at the
 // two waves per SIMD that the tap coefficients in registers leave.
 //
-// Widths up to 12: the window leaves an origin span of 17 - W cells, BS the power of
-// two within it (8 up to W = 8, else 4).  W = 14 and 16 would leave blocks of 2 and 1
+// Widths 8 to 12: the window leaves an origin span of 17 - W cells, BS the power of
+// two within it (8 at W = 8, else 4).  W = 14 and 16 would leave blocks of 2 and 1
 // cells, mostly padding unless a cell holds tens of points; they keep the kernels
-// above, as do plans without the tap polynomials.
+// of one point per lane, as do narrower kernels, sparse cells (m64_use) and plans without
+// the tap polynomials.
 #pragma once
 
 typedef double mfma_d4 __attribute__((ext_vector_type(4)));
@@ -383,8 +384,21 @@ constexpr size_t m64_lds(bool gather) {
          sizeof(uint16_t) * M64<W>::list(nt, gather ? 16 : 4);
 }
 
-// Whether a plan's FP64 unit passes run on the matrix cores, and their launches.
-inline bool m64_use(int W, const EsPoly64 &es64) { return es64.on && W <= 12 && W % 2 == 0; }
+// Whether a cell's FP64 unit passes run on the matrix cores, and their launches.
+//
+// The blocks' padding, and a workgroup's list and its one place per CU, cost 4 (spreading)
+// to 9 us (gather) per tile of a CU more than the kernels of one point per lane; what is
+// won grows with the points that share a tile's cells.  Both forms, us (type-1, adjoint),
+// W = 12, clustered points on 1,024 tiles: 35 points a tile 180 and 186, 211 and 217; 100
+// 208 and 192, 281 and 232; 300 294 and 204, 441 and 290.  Even points lose until about 200
+// to 400 a tile (100: 184 and 192, 216 and 244; 450: 216 and 213, 273 and 274).  On 4,096 tiles, where
+// each CU takes sixteen, 100 clustered points 354 and 380, 532 and 563; 200 468 and 404,
+// 727 and 646; even ones 381 and 406 at 200.  W = 8 and 10 lie close to this.  At W = 6 and
+// below nothing is won (1e6 clustered points 323 and 315; 700 a tile 290 and 296, even 206 and 222).
+constexpr double M64_PER_TILE = 96.0, M64_PER_TILE_MANY = 200.0;
+inline bool m64_use(enufft_plan_t p, const EsPoly64 &es64, int64_t n) {
+  return es64.on && p->W >= 8 && p->W <= 12 && (double)n >= p->m64_per_tile * p->big_ntx * p->big_nty;
+}
 
 template <int W>
 hipError_t m64_launch_w(const BigTileArgs<double> &a, bool gather, int blocks, hipStream_t s) {
@@ -395,8 +409,6 @@ hipError_t m64_launch_w(const BigTileArgs<double> &a, bool gather, int blocks, h
 
 inline hipError_t m64_launch(int W, const BigTileArgs<double> &a, bool gather, int blocks, hipStream_t s) {
   switch (W) {
-    case 4: return m64_launch_w<4>(a, gather, blocks, s);
-    case 6: return m64_launch_w<6>(a, gather, blocks, s);
     case 8: return m64_launch_w<8>(a, gather, blocks, s);
     case 10: return m64_launch_w<10>(a, gather, blocks, s);
     case 12: return m64_launch_w<12>(a, gather, blocks, s);
@@ -413,9 +425,7 @@ hipError_t m64_attr_w() {
                              (int)m64_lds<W>(true));
 }
 inline hipError_t m64_attrs() {
-  hipError_t e = m64_attr_w<4>();
-  if (e == hipSuccess) e = m64_attr_w<6>();
-  if (e == hipSuccess) e = m64_attr_w<8>();
+  hipError_t e = m64_attr_w<8>();
   if (e == hipSuccess) e = m64_attr_w<10>();
   if (e == hipSuccess) e = m64_attr_w<12>();
   return e;

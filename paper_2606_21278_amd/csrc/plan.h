@@ -131,6 +131,7 @@ struct enufft_plan_s {
   void *big_xs = nullptr, *big_ys = nullptr, *big_hs = nullptr, *big_ws = nullptr;
   double *big_partial = nullptr;             // [units][S x S] FP64 sub-grids of the spreading units
   int64_t big_units_max = 0;
+  double m64_per_tile = 0.0;       // FP64 unit passes on the matrix cores: fewest points per tile
   void *big_gout = nullptr;                  // [largest cell] gradients in sorted order (4-vectors)
   double *big_grid = nullptr;                // n2 x n1 FP64 spreading grid
   void *big_cb = nullptr, *big_cby = nullptr;   // column buffers [K1 + 1][n2] complex
