@@ -752,12 +752,15 @@ enufft_status enufft_plan(enufft_plan_t *out, int64_t n_cells, const int64_t *ce
   // ---- forward launch shape (threads per workgroup: ENUFFT_FWD_THREADS, or the autotuner)
   enufft_status st = ENUFFT_OK;
   if (!big) {
-    // Sixteen waves per CU hide the FP32 runs' latency better than eight (20,480 triangles
-    // of 40,000 points on the 128-wide grid: 7.57 ms at 512 threads, 7.15 at 1,024; 3,000
-    // of them 972 to 918 us, 4,000 hexagons of 30,000 points in no order 3,045 to 3,031),
-    // but their 128 registers spill beside the runs, which shows where a cell's points
-    // do not outweigh its transform (4,000 cells of 600 points: 336 us against 350) or a
-    // workgroup takes few cells (1,500 of 3,300 points: 185 against 197).
+    // Sixteen waves per CU hide the FP32 runs' latency better than eight, but their 128
+    // registers spill beside the runs, and one workgroup per CU does not spread one cell
+    // while another transforms.  512 against 1,024 threads, us, raster points: 2,100 cells of
+    // 40,000 825 and 753 (W = 6), 600 and 554 (W = 4); 3,100 of mean 18,500 in a lognormal
+    // spread 701 and 689; 8,200 of mean 13,300 1,505 and 1,498 (W = 4: 1,134 and 1,100), of
+    // mean 8,800 1,249 and 1,269 (964 and 950).  The line lies below those spreads; cells of
+    // one size would want it at 14,000 (8,200 of 14,000 1,547 and 1,547, of 9,000 1,215 and
+    // 1,331).  Points in no order differ by 1 % or less but there.  A workgroup that takes
+    // few cells loses (1,500 cells of 3,300 points: 185 and 197).
     int threads = 512;
     if (p->prec == ENUFFT_F32 && W <= 6 && p->es.on && g.pitch == enufft::FWD_PITCH128 &&
         n_cells >= 8 * (int64_t)p->n_cu && p->n_points >= 8192 * (int64_t)n_cells)
