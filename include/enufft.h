@@ -149,7 +149,7 @@ typedef struct {
                                 FP64 plans), 0 if the kernel itself is evaluated */
     int32_t tuned;           /* 1 if the autotuner set the launch shape */
     int32_t tune_cache_hit;  /* 1 if that choice came from the on-disk cache */
-    int64_t fwd_chunk_min;   /* smallest forward work item (points) */
+    int64_t fwd_chunk_min;   /* smallest forward work item a cell is cut into (points) */
     int32_t fwd_items_per_slot, adj_items_per_slot;  /* work items per resident workgroup */
     int32_t adj_band_mult;   /* adjoint row bands = this x the fewest that fit LDS */
     int32_t fwd_acc;         /* bytes per forward LDS grid cell: 8 (FP64 sums) or 4 (FP32 sums) */
@@ -216,8 +216,8 @@ enufft_status enufft_type1_batched_noalloc(enufft_plan_t p, const void *x, const
  *               sum |f_k|^2.  Energies, sums and the cumulative threshold are FP64.
  * Units are ordered by descending energy, ties by ascending row-major index of
  * the unit's representative (the member with k_y > 0, or k_y = 0 and k_x > 0).
- * Up to 4096 units per cell are sorted in registers by one workgroup per cell;
- * more take a device bitonic sort per cell. */
+ * Up to 4096 units per cell are sorted by one workgroup per cell, in LDS; more take a
+ * device bitonic sort per cell. */
 enufft_status enufft_ems(enufft_plan_t p, const void *f, const enufft_ems_params *prm,
                          const double *mode_weight, uint8_t *keep, int32_t *k_star, double *stats);
 

@@ -72,8 +72,8 @@ __device__ __forceinline__ void stage_spectrum(const AdjArgs<T> &a, const T *gc,
 // row, natural order) of column kx of the Hermitian, pre-corrected spectrum
 // from the staged copy: (G(kx, ky) + conj G(-kx, -ky)) / 2 divided by the
 // kernel transform, each term zero outside the mode box, with the
-// retained-power factor two_lam on kept modes (1 without a keep mask); with
-// yderiv, times i ky.  store() writes the column workspace.
+// retained-power factor two_lam on kept modes (1 without a keep mask).  store()
+// writes the column workspace.
 template <typename T>
 struct ColSpecAcc {
   const T *sf, *sdx, *sdy;
@@ -81,7 +81,6 @@ struct ColSpecAcc {
   T two_lam;
   T *col;   // column kx of the workspace (interleaved complex, row pitch cpitch)
   int cpitch, kx, n2, K2, N1, lo1, lo2, hi1, hi2;
-  bool yderiv;
   __device__ void load(int bin, T &re, T &im) const {
     const int ky = bin <= n2 / 2 ? bin : bin - n2;   // signed frequency of this bin
     T hr = 0, hi = 0;
@@ -101,11 +100,6 @@ struct ColSpecAcc {
       }
       hr *= T(0.5) * s;
       hi *= T(0.5) * s;
-      if (yderiv) {
-        const T t = hr;
-        hr = -T(ky) * hi;
-        hi = T(ky) * t;
-      }
     }
     re = hr;
     im = hi;
@@ -146,12 +140,12 @@ __device__ __forceinline__ void col_step2_band(const T *col, int cpitch, int k1,
   }
 }
 
-// One column pass: the inverse transforms along y of columns kx = 0..K1 of the
-// spectrum (times i ky with yderiv), formed from the staged copy in the first
-// step and written to the band spectra db by the second.
+// The column pass: the inverse transforms along y of columns kx = 0..K1 of the
+// spectrum, formed from the staged copy in the first step and written to the band
+// spectra db by the second.
 template <typename T, int NT>
 __device__ __forceinline__ void column_pass(const AdjArgs<T> &a, const T *st, const T *tw2, T two_lam, T *ws, int cpitch,
-                            bool yderiv, T *db, int rows, int y0) {
+                                            T *db, int rows, int y0) {
   const Geom &g = a.g;
   const int per = g.K1 + 1, n2 = g.n2, M = g.N1 * g.N2;
   const int A = fft_A(n2), B = fft_B(n2);
@@ -164,7 +158,6 @@ __device__ __forceinline__ void column_pass(const AdjArgs<T> &a, const T *st, co
   acc.cpitch = cpitch;
   acc.n2 = n2; acc.K2 = g.K2; acc.N1 = g.N1; acc.lo1 = g.lo1; acc.lo2 = g.lo2;
   acc.hi1 = g.lo1 + g.N1 - 1; acc.hi2 = g.lo2 + g.N2 - 1;
-  acc.yderiv = yderiv;
   // Consecutive lanes take consecutive columns (the column is the fast index of
   // both steps), so their LDS words are adjacent: the staged coefficients of
   // consecutive kx, the workspace elements 2 kx apart, the band spectra of
@@ -868,10 +861,12 @@ static const void *adj_fn_w(int W, bool poly, bool recon) {
 
 // ------------------------------------------------------------------ FP32 reconstruction
 //
-// FP32 plans reconstruct from rows of (u, du/dx) like the gradients' (the imaginary
-// half unused), in row bands that transform their own columns.  The per-cell sums of
-// squared residuals are FP64 sums of FP32 residuals, so they follow every rounding
-// of u: the pairing of rows that serves FP64 above changes them by about 5e-8.
+// FP32 plans reconstruct from rows of (u, du/dx) like the gradients' (the du/dx half is
+// transformed beside u and not read), in row bands that transform their own columns.  The
+// pairing of rows that serves FP64 above would round u differently, by about 5e-8, which
+// the per-cell FP64 sums of squared FP32 residuals follow; the same row transforms with
+// only their real parts stored would give u's bits in half the LDS and a single band at
+// the 64 x 64 box, and are not built.
 
 struct RecLayout {
   int rows;       // band rows including halo = band_rows + W
@@ -901,36 +896,26 @@ __host__ __device__ inline RecLayout rec_layout(const Geom &g, int W, int band_r
 }
 
 // First-step accessor of its row transforms: bin k of the row's spectrum (1 - k) D(k)
-// from the band's column data db ([row][kx] complex).
+// from the band's column data db ([row][kx] complex); store() writes the row's pairs.
 template <typename T>
 struct RecSpecAcc {
-  const T *db;
-  T *r0, *r1;
-  int stride, row, per, n1, K1;
-  bool pair;
+  const T *db;   // the row's column data
+  T *r;
+  int n1, K1;
   __device__ void load(int k, T &re, T &im) const {
     const int kk = k <= n1 / 2 ? k : n1 - k;
     re = T(0);
     im = T(0);
     if (kk > K1) return;
     const bool neg = k != kk;
-    const T *d = db + 2 * (row * per + kk);
-    T dr = d[0], di = d[1];
-    if (neg) di = -di;
-    if (!pair) {
-      const T kf = neg ? -T(kk) : T(kk);
-      re = dr - kf * dr;
-      im = di - kf * di;
-    } else {
-      T br = d[2 * per], bi = d[2 * per + 1];
-      if (neg) bi = -bi;
-      re = dr - bi;
-      im = di + br;
-    }
+    const T dr = db[2 * kk], di = neg ? -db[2 * kk + 1] : db[2 * kk + 1];
+    const T kf = neg ? -T(kk) : T(kk);
+    re = dr - kf * dr;
+    im = di - kf * di;
   }
   __device__ void store(int i, T re, T im) const {
-    r0[i * stride] = re;
-    r1[i * stride] = im;
+    r[2 * i] = re;
+    r[2 * i + 1] = im;
   }
 };
 
@@ -1061,45 +1046,16 @@ __global__ __launch_bounds__(ADJ_THREADS) void rec_kernel(AdjArgs<float> a) {
     const int y0 = it.band * a.band_rows;   // fine row of band-local row 0
     T *st = sm + L.st_off;
     stage_spectrum<T, NT>(a, gc, it.cell, st);
-    column_pass<T, NT>(a, st, tw2, T(1), ws, L.cpitch, false, db, L.rows, y0);
+    column_pass<T, NT>(a, st, tw2, T(1), ws, L.cpitch, db, L.rows, y0);
     // the (u, du/dx) rows, spectrum (1 - k) D(k)
-    float *db0 = db, *db1 = db, *Gy = Guv;
-    constexpr bool RECON = true;
-    const int n1 = g.n1;
-    const int ny_pairs = L.rows / 2;
-    const int K1 = g.K1;
     row_ifft_natural<NT, T>(
-        n1, RECON ? L.rows : L.rows + ny_pairs, tw1, W - 1,
-        [&](int q) {
-          RecSpecAcc<T> acc;
-          acc.db = q < L.rows ? db0 : db1;
-          acc.row = q < L.rows ? q : 2 * (q - L.rows);
-          acc.pair = q >= L.rows;
-          acc.per = per;
-          acc.n1 = n1;
-          acc.K1 = K1;
-          if (q < L.rows) {
-            acc.r0 = Guv + 2 * q * pitch;
-            acc.r1 = acc.r0 + 1;
-            acc.stride = 2;
-          } else {
-            acc.r0 = Gy + 2 * (q - L.rows) * pitch;
-            acc.r1 = acc.r0 + pitch;
-            acc.stride = 1;
-          }
-          return acc;
-        },
+        g.n1, L.rows, tw1, W - 1,
+        [&](int q) { return RecSpecAcc<T>{db + 2 * q * per, Guv + 2 * q * pitch, g.n1, g.K1}; },
         [&](int q) {
           StridedPairAcc<T> acc;
-          if (q < L.rows) {
-            acc.r0 = Guv + 2 * q * pitch;
-            acc.r1 = acc.r0 + 1;
-            acc.stride = 2;
-          } else {
-            acc.r0 = Gy + 2 * (q - L.rows) * pitch;
-            acc.r1 = acc.r0 + pitch;
-            acc.stride = 1;
-          }
+          acc.r0 = Guv + 2 * q * pitch;
+          acc.r1 = acc.r0 + 1;
+          acc.stride = 2;
           return acc;
         });
 
@@ -1431,7 +1387,7 @@ __global__ __launch_bounds__(NT, (NT == 512 ? 4 : 1)) void adj1_kernel(AdjArgs<f
     const float two_lam = a.keep ? float(2.0 * (a.lam ? a.lam[it.cell] : 1.0)) : 1.0f;
     stage_spectrum<float, NT>(a, gc, it.cell, st);
     // columns kx = 0 .. K1 of the pre-corrected spectrum, inverse transformed along y
-    column_pass<float, NT>(a, st, tw2, two_lam, ws, L.cpitch, false, db, g.n2, 0);
+    column_pass<float, NT>(a, st, tw2, two_lam, ws, L.cpitch, db, g.n2, 0);
     // rows in pairs: Z(k) = D_2q(k) + i D_2q+1(k) gives rows 2q and 2q + 1 as its real
     // and imaginary parts (both rows' spectra are Hermitian)
     const int n1 = g.n1, K1 = g.K1;
@@ -1667,14 +1623,8 @@ static enufft_status cols_prepare(enufft_plan_t p) {
 // Set up a banded schedule on first use (the gradients' or the reconstruction's).
 static enufft_status band_prepare(enufft_plan_t p, AdjSched *s, bool recon) {
   if (s->ready) return ENUFFT_OK;
-  hipDeviceProp_t prop;
-  hipError_t e = hipGetDeviceProperties(&prop, p->device);
-  if (e != hipSuccess) {
-    p->last_error = std::string("hipGetDeviceProperties: ") + hipGetErrorString(e);
-    return ENUFFT_EDEVICE;
-  }
   AdjSched n;
-  int B = choose_bands(p->geom, p->W, p->elem, recon, (size_t)prop.sharedMemPerBlock, &n.band_rows, &n.lds);
+  int B = choose_bands(p->geom, p->W, p->elem, recon, p->lds_limit, &n.band_rows, &n.lds);
   if (B == 0) {
     p->last_error = "adjoint: fine-grid bands do not fit in LDS";
     return ENUFFT_EUNSUPPORTED;
@@ -1721,25 +1671,20 @@ enufft_status cell_offsets(enufft_plan_t p) {
   return adj_upload(p, &p->d_cell_off, p->offsets.data(), p->offsets.size() * sizeof(int64_t), "cell offsets");
 }
 
-// Large-cell plans offer the mesh geometry only while a row band of two rows with
-// its cell's column workspace, staged spectrum and band spectra fits one
-// workgroup's LDS (grids up to 256 per axis, about).
+// Large-cell plans offer the mesh geometry on the grids they have always offered it on,
+// up to 256 per axis, about: those where a row band of two rows with its cell's column
+// workspace, staged spectrum and band spectra would fit one workgroup's LDS.  (The
+// geometry itself needs the cell offsets and its bins only.)
 enufft_status geometry_supported(enufft_plan_t p) {
   if (!p->big) return ENUFFT_OK;
-  hipDeviceProp_t prop;
-  const hipError_t e = hipGetDeviceProperties(&prop, p->device);
-  if (e != hipSuccess) {
-    p->last_error = std::string("hipGetDeviceProperties: ") + hipGetErrorString(e);
-    return ENUFFT_EDEVICE;
-  }
   const Geom &g = p->geom;
   for (int R = g.n2; R >= 2; R >>= 1) {
     const size_t rows = (size_t)R + p->W, apitch = (size_t)((g.n1 + p->W) & ~1), per = g.K1 + 1;
     const size_t cols = (size_t)g.n2 * (2 * per + 2) + adj_stage_elems(g, p->elem);
     const size_t total = std::max(3 * rows * apitch, cols) + 4 * rows * per + 2 * (size_t)(g.n1 + g.n2);
-    if (total * p->elem <= prop.sharedMemPerBlock) return ENUFFT_OK;
+    if (total * p->elem <= p->lds_limit) return ENUFFT_OK;
   }
-  p->last_error = "adjoint: fine-grid bands do not fit in LDS";
+  p->last_error = "enufft_cell_geometry: not offered for a large-cell plan of this fine grid";
   return ENUFFT_EUNSUPPORTED;
 }
 
@@ -1827,7 +1772,6 @@ static hipError_t launch_band(enufft_plan_t p, AdjArgs<T> a, const AdjSched &s) 
   const void *fn = band_fn(p, recon);
   const int nset = recon ? 1 : 2, ngrp = adj_col_groups(a.g), cg = (a.g.K1 + 1 + ngrp - 1) / ngrp;
   const size_t lds_cols = ((size_t)a.g.n2 * (2 * cg + 2) + 2 * (size_t)a.g.n2) * sizeof(T);
-  a.bands = s.bands;
   a.band_rows = s.band_rows;
   a.cols = (T *)p->d_adj_cols;
   double *part = a.rec_part;

@@ -123,7 +123,7 @@ struct AdjArgs {
   EsPoly es;                   // as in FwdArgs (the single-grid adjoint: its own kernel's taps)
   Poly64Of<T> es64;
   T dsx, dsy;                  // single-grid adjoint: -2 n1 / (2 pi), -2 n2 / (2 pi)
-  int bands, band_rows;        // row bands per cell and rows per band
+  int band_rows;               // rows per band
   T *cols;                     // banded adjoint: column spectra of cells cell0 .. (see adj_cols_kernel)
   int cell0;
   double *rec_part;            // reconstruction mode: per item (sum (t - h_rec)^2, sum t^2, sum w t^2)

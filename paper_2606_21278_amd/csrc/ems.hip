@@ -1,5 +1,6 @@
-// Elastic Mode Selection on gfx950: one workgroup per cell; the unit energies
-// are sorted in registers per wave and merged through LDS.
+// Elastic Mode Selection on gfx950: one workgroup per cell; the unit energies stay in
+// registers and their values are placed in LDS by bucket and rank (cells whose buckets
+// crowd, or with negative energies: a comparison network per wave, merged through LDS).
 //
 // Section 2.2 of the paper, in its order: unit energies (eq. energy, with the
 // optional weight of eq. weighted_e), the descending order of eq.
@@ -351,7 +352,9 @@ constexpr int EMS_BUCKET_MAX = 64;
 // coefficients and masks).  With the network for every cell, each thread's units
 // consecutive (64 cache lines per load) and the coefficients and a unit record per
 // mode read again for the keep flags the launch took 0.88 ms; now 0.56 ms (and
-// eight flow steps of 2,560 cells 1.31 to 0.53 ms).
+// eight flow steps of 2,560 cells 1.31 to 0.53 ms).  A cell that falls back pays for both:
+// equal amplitudes in every mode, 20,480 cells, 0.87 ms (0.89 with the network alone) at 2,111 units,
+// 0.31 (0.235) at 512; four cells 27.2 us (24.6).
 template <typename T, int R, int NW>
 __global__ __launch_bounds__(64 * NW, (ems_min_waves<NW>())) void ems_kernel(EmsArgs a) {
   constexpr int NT = 64 * NW, JW = 64 * R, JP = JW * NW;
@@ -769,8 +772,6 @@ enufft_status ems_validate(enufft_plan_t p, const void *f, const enufft_ems_para
   return ENUFFT_OK;
 }
 
-// Sort size per cell: the smallest 64 R NW >= J (R a power of two up to 16,
-// then 1 to 4 waves of 1,024).
 // Whether a launch of `blocks` cells leaves the CUs mostly idle with the narrow
 // forms (fewer than eight of their waves per CU): then the wide forms.
 // ENUFFT_EMS_WIDE=0 or 1 forces the choice.
@@ -786,6 +787,8 @@ static hipError_t launch_ems_form(const EmsArgs &a, int J, int blocks, hipStream
   return hipGetLastError();
 }
 
+// The form of a cell: the smallest 64 R NW >= J, R values a lane (a power of two up to
+// 16) and NW waves (up to 4), or the wide forms' four values and up to 16 waves.
 template <typename T>
 hipError_t launch_ems_t(const EmsArgs &a, int J, int blocks, hipStream_t s, bool wide) {
   if (wide && J > 256) {

@@ -672,6 +672,7 @@ enufft_status enufft_plan(enufft_plan_t *out, int64_t n_cells, const int64_t *ce
   e = hipGetDeviceProperties(&prop, p->device);
   if (e != hipSuccess) { enufft_status s = hip_fail(p, e, "hipGetDeviceProperties"); free_plan(p); return s; }
   p->n_cu = prop.multiProcessorCount;
+  p->lds_limit = (size_t)prop.sharedMemPerBlock;
 
   // FP32 plans evaluate the kernel as per-tap polynomials when the fit is far
   // below the requested accuracy (it is for the compiled widths 4..8).

@@ -51,6 +51,8 @@ struct enufft_plan_s {
   enufft_opts opts{};              // as given to enufft_plan
   std::vector<enufft_window> windows_host;
 
+  size_t lds_limit = 0;            // the device's LDS per workgroup (bytes)
+
   // launch-shape parameters (defaults, or chosen by the autotuner)
   int64_t fwd_chunk_min = 16384;   // smallest forward work item (points)
   bool fwd_chunk_auto = true;      // FP64: smaller ones where workgroups would idle
