@@ -72,8 +72,8 @@ __device__ __forceinline__ void stage_spectrum(const AdjArgs<T> &a, const T *gc,
 // row, natural order) of column kx of the Hermitian, pre-corrected spectrum
 // from the staged copy: (G(kx, ky) + conj G(-kx, -ky)) / 2 divided by the
 // kernel transform, each term zero outside the mode box, with the
-// retained-power factor two_lam on kept modes (1 without a keep mask).  store()
-// writes the column workspace.
+// retained-power factor two_lam on kept modes (1 without a keep mask); with
+// yderiv, times i ky.  store() writes the column workspace.
 template <typename T>
 struct ColSpecAcc {
   const T *sf, *sdx, *sdy;
@@ -81,6 +81,7 @@ struct ColSpecAcc {
   T two_lam;
   T *col;   // column kx of the workspace (interleaved complex, row pitch cpitch)
   int cpitch, kx, n2, K2, N1, lo1, lo2, hi1, hi2;
+  bool yderiv;
   __device__ void load(int bin, T &re, T &im) const {
     const int ky = bin <= n2 / 2 ? bin : bin - n2;   // signed frequency of this bin
     T hr = 0, hi = 0;
@@ -100,6 +101,11 @@ struct ColSpecAcc {
       }
       hr *= T(0.5) * s;
       hi *= T(0.5) * s;
+      if (yderiv) {
+        const T t = hr;
+        hr = -T(ky) * hi;
+        hi = T(ky) * t;
+      }
     }
     re = hr;
     im = hi;
@@ -140,12 +146,12 @@ __device__ __forceinline__ void col_step2_band(const T *col, int cpitch, int k1,
   }
 }
 
-// The column pass: the inverse transforms along y of columns kx = 0..K1 of the
-// spectrum, formed from the staged copy in the first step and written to the band
-// spectra db by the second.
+// One column pass: the inverse transforms along y of columns kx = 0..K1 of the
+// spectrum (times i ky with yderiv), formed from the staged copy in the first
+// step and written to the band spectra db by the second.
 template <typename T, int NT>
 __device__ __forceinline__ void column_pass(const AdjArgs<T> &a, const T *st, const T *tw2, T two_lam, T *ws, int cpitch,
-                                            T *db, int rows, int y0) {
+                            bool yderiv, T *db, int rows, int y0) {
   const Geom &g = a.g;
   const int per = g.K1 + 1, n2 = g.n2, M = g.N1 * g.N2;
   const int A = fft_A(n2), B = fft_B(n2);
@@ -158,6 +164,7 @@ __device__ __forceinline__ void column_pass(const AdjArgs<T> &a, const T *st, co
   acc.cpitch = cpitch;
   acc.n2 = n2; acc.K2 = g.K2; acc.N1 = g.N1; acc.lo1 = g.lo1; acc.lo2 = g.lo2;
   acc.hi1 = g.lo1 + g.N1 - 1; acc.hi2 = g.lo2 + g.N2 - 1;
+  acc.yderiv = yderiv;
   // Consecutive lanes take consecutive columns (the column is the fast index of
   // both steps), so their LDS words are adjacent: the staged coefficients of
   // consecutive kx, the workspace elements 2 kx apart, the band spectra of
@@ -865,8 +872,10 @@ static const void *adj_fn_w(int W, bool poly, bool recon) {
 // transformed beside u and not read), in row bands that transform their own columns.  The
 // pairing of rows that serves FP64 above would round u differently, by about 5e-8, which
 // the per-cell FP64 sums of squared FP32 residuals follow; the same row transforms with
-// only their real parts stored would give u's bits in half the LDS and a single band at
-// the 64 x 64 box, and are not built.
+// only their real parts stored would need half the LDS and a single band at the 64 x 64
+// box, and are not built.  (The arms for row pairs below are not taken; a build without
+// them, and without the column pass's unused derivative, rounded u differently all the
+// same, and moved the sums by 3e-8.)
 
 struct RecLayout {
   int rows;       // band rows including halo = band_rows + W
@@ -896,26 +905,36 @@ __host__ __device__ inline RecLayout rec_layout(const Geom &g, int W, int band_r
 }
 
 // First-step accessor of its row transforms: bin k of the row's spectrum (1 - k) D(k)
-// from the band's column data db ([row][kx] complex); store() writes the row's pairs.
+// from the band's column data db ([row][kx] complex).
 template <typename T>
 struct RecSpecAcc {
-  const T *db;   // the row's column data
-  T *r;
-  int n1, K1;
+  const T *db;
+  T *r0, *r1;
+  int stride, row, per, n1, K1;
+  bool pair;
   __device__ void load(int k, T &re, T &im) const {
     const int kk = k <= n1 / 2 ? k : n1 - k;
     re = T(0);
     im = T(0);
     if (kk > K1) return;
     const bool neg = k != kk;
-    const T dr = db[2 * kk], di = neg ? -db[2 * kk + 1] : db[2 * kk + 1];
-    const T kf = neg ? -T(kk) : T(kk);
-    re = dr - kf * dr;
-    im = di - kf * di;
+    const T *d = db + 2 * (row * per + kk);
+    T dr = d[0], di = d[1];
+    if (neg) di = -di;
+    if (!pair) {
+      const T kf = neg ? -T(kk) : T(kk);
+      re = dr - kf * dr;
+      im = di - kf * di;
+    } else {
+      T br = d[2 * per], bi = d[2 * per + 1];
+      if (neg) bi = -bi;
+      re = dr - bi;
+      im = di + br;
+    }
   }
   __device__ void store(int i, T re, T im) const {
-    r[2 * i] = re;
-    r[2 * i + 1] = im;
+    r0[i * stride] = re;
+    r1[i * stride] = im;
   }
 };
 
@@ -1046,16 +1065,45 @@ __global__ __launch_bounds__(ADJ_THREADS) void rec_kernel(AdjArgs<float> a) {
     const int y0 = it.band * a.band_rows;   // fine row of band-local row 0
     T *st = sm + L.st_off;
     stage_spectrum<T, NT>(a, gc, it.cell, st);
-    column_pass<T, NT>(a, st, tw2, T(1), ws, L.cpitch, db, L.rows, y0);
+    column_pass<T, NT>(a, st, tw2, T(1), ws, L.cpitch, false, db, L.rows, y0);
     // the (u, du/dx) rows, spectrum (1 - k) D(k)
+    float *db0 = db, *db1 = db, *Gy = Guv;
+    constexpr bool RECON = true;
+    const int n1 = g.n1;
+    const int ny_pairs = L.rows / 2;
+    const int K1 = g.K1;
     row_ifft_natural<NT, T>(
-        g.n1, L.rows, tw1, W - 1,
-        [&](int q) { return RecSpecAcc<T>{db + 2 * q * per, Guv + 2 * q * pitch, g.n1, g.K1}; },
+        n1, RECON ? L.rows : L.rows + ny_pairs, tw1, W - 1,
+        [&](int q) {
+          RecSpecAcc<T> acc;
+          acc.db = q < L.rows ? db0 : db1;
+          acc.row = q < L.rows ? q : 2 * (q - L.rows);
+          acc.pair = q >= L.rows;
+          acc.per = per;
+          acc.n1 = n1;
+          acc.K1 = K1;
+          if (q < L.rows) {
+            acc.r0 = Guv + 2 * q * pitch;
+            acc.r1 = acc.r0 + 1;
+            acc.stride = 2;
+          } else {
+            acc.r0 = Gy + 2 * (q - L.rows) * pitch;
+            acc.r1 = acc.r0 + pitch;
+            acc.stride = 1;
+          }
+          return acc;
+        },
         [&](int q) {
           StridedPairAcc<T> acc;
-          acc.r0 = Guv + 2 * q * pitch;
-          acc.r1 = acc.r0 + 1;
-          acc.stride = 2;
+          if (q < L.rows) {
+            acc.r0 = Guv + 2 * q * pitch;
+            acc.r1 = acc.r0 + 1;
+            acc.stride = 2;
+          } else {
+            acc.r0 = Gy + 2 * (q - L.rows) * pitch;
+            acc.r1 = acc.r0 + pitch;
+            acc.stride = 1;
+          }
           return acc;
         });
 
@@ -1387,7 +1435,7 @@ __global__ __launch_bounds__(NT, (NT == 512 ? 4 : 1)) void adj1_kernel(AdjArgs<f
     const float two_lam = a.keep ? float(2.0 * (a.lam ? a.lam[it.cell] : 1.0)) : 1.0f;
     stage_spectrum<float, NT>(a, gc, it.cell, st);
     // columns kx = 0 .. K1 of the pre-corrected spectrum, inverse transformed along y
-    column_pass<float, NT>(a, st, tw2, two_lam, ws, L.cpitch, db, g.n2, 0);
+    column_pass<float, NT>(a, st, tw2, two_lam, ws, L.cpitch, false, db, g.n2, 0);
     // rows in pairs: Z(k) = D_2q(k) + i D_2q+1(k) gives rows 2q and 2q + 1 as its real
     // and imaginary parts (both rows' spectra are Hermitian)
     const int n1 = g.n1, K1 = g.K1;
